@@ -12,6 +12,7 @@ namespace nep {
 
 constexpr int kMaxTerms = 16;
 constexpr int kBandMax = 64;  // widest half-bandwidth kept in band form
+constexpr int kNarrowMax = 4;  // widest band of the band path (band.hip)
 constexpr int kLowRankMax = 96;  // largest rank kept in factored form
 constexpr int kMaxMoments = 32;  // 2K
 constexpr int kSolveBlk = 64;    // triangular-solve block rows
@@ -62,6 +63,8 @@ struct ProbDesc {
   long long s_stride;     // elements between consecutive moment blocks of S (>= n*L)
   int active;             // 0: the problem sits out this pass on resident factors (its
                           // nodes count as converged, its V and S are not touched)
+  int band;               // 0: dense factors; else the band path's window half-width (1, 2 or 4)
+  long long offF, offP;   // its factor (elements) and pivot bytes
   const c128* fpts;       // with zpts: given coefficients in place of f_i(z_j), at
                           // fpts[j*ell + i] (device), or nullptr
 };
@@ -132,6 +135,32 @@ struct ProblemTables {
 
 void build_prefix(std::vector<int>& buf, Table& t, const std::vector<int>& counts);
 
+// The band path (band.hip): launch tables per window half-width 1, 2, 4, over
+// the plan's problems (zero counts for the others).
+constexpr int kBandClasses = 3;
+struct BandTables {
+  Table assemble[kBandClasses], lu[kBandClasses], solve[kBandClasses], resid[kBandClasses], node[kBandClasses];
+};
+int band_class(int w);    // window half-width (1, 2 or 4) that holds a band of half-width w <= kNarrowMax
+int band_entries(int W);  // stored entries per row and node
+void band_tables(BandTables& bt, std::vector<int>& buf, const std::vector<ProbDesc>& pd);
+// assembly and factorization of every band problem's nodes (skip: nodes left
+// out); info: first zero pivot or n, pmin: smallest pivot modulus, per node
+template <typename P>
+hipError_t band_factor(const BandTables& bt, const ProbDesc* pd, const int* prefix, const NodeArrays& na, cx<P>* F,
+                       unsigned char* piv, int* info, double* pmin, const int* skip, hipStream_t st);
+// kBandV: Y = T^{-1} V; kBandR: Y = T^{-1} R; kBandRefine: Y += T^{-1} R, R overwritten
+enum { kBandV = 0, kBandR = 1, kBandRefine = 2 };
+template <typename P>
+hipError_t band_solve(const BandTables& bt, const ProbDesc* pd, const int* prefix, const cx<P>* F,
+                      const unsigned char* piv, c128* R, c128* Y, int mode, const int* conv, IrState ir,
+                      hipStream_t st);
+hipError_t band_resid(const BandTables& bt, const ProbDesc* pd, const int* prefix, const NodeArrays& na,
+                      const c128* Y, c128* R, IrState ir, hipStream_t st);
+template <typename P>
+hipError_t band_logdet(const BandTables& bt, const ProbDesc* pd, const int* prefix, const cx<P>* F,
+                       const unsigned char* piv, int nnodes, double* out, hipStream_t st);
+
 // Kernel launchers (all asynchronous on st).
 hipError_t launch_coef(const ProbDesc* pd, const NodeArrays& na, int nnodes, IrState ir, hipStream_t st);
 template <typename P>
@@ -167,7 +196,9 @@ hipError_t resid_run(const ProbDesc* pd, const int* prefix, const Table& t, cons
                      int nlr = 0);
 // status read-back block (see k_gather_status) and its size
 size_t status_bytes(int G);
-hipError_t gather_status(IrState ir, const int* info, const int* bad, int G, void* out, hipStream_t st);
+// (pmin: smallest pivot moduli to start from, or nullptr: see min_pivot)
+hipError_t gather_status(IrState ir, const int* info, const int* bad, const double* pmin, int G, void* out,
+                         hipStream_t st);
 // smallest pivot modulus per node into the status block (after rho)
 template <typename P>
 hipError_t min_pivot(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, int G, void* status,

@@ -1670,6 +1670,7 @@ hipError_t lu_run(const LuPlan& plan, const MatDesc* d_md, const int* d_prefix, 
   hipStream_t aux = ls.aux, side = ls.side;
   hipEvent_t ev_fork = ls.ev_fork, ev_join = ls.ev_join;
   hipError_t e;
+  if (plan.nmat == 0) return hipSuccess;
   hipLaunchKernelGGL(k_lu_init, dim3(plan.nmat), dim3(256), 0, st, d_md, plan.nmat, rows, info);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int nsteps = (int)plan.steps.size();

@@ -1216,6 +1216,7 @@ nep_status nep_nleigs(nep_split h, const nep_contour* g, const nep_nleigs_opts* 
   po.prec = NEP_PREC_FP64;
   po.max_refine = 0;
   po.fallback = 0;
+  po.dense = true;  // the solves below read the dense factor
   PlanProblem pp{&s.op, g0, nullptr, nullptr, dsig.as<c128>()};
   pp.fpts = drho.as<c128>();
   std::vector<PlanProblem> probs{pp};

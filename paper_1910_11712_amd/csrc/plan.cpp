@@ -184,6 +184,20 @@ bool MomentsPlan::matches(const std::vector<PlanProblem>& probs, const PlanOptio
   return true;
 }
 
+// Window half-width of the band path when every term of the operator is
+// diagonal or real banded with a half-width of at most kNarrowMax; 0: dense.
+// (Complex terms are marked diagonal or dense at creation, real ones also
+// banded; device matrices are not inspected and stay dense.)
+static int band_of(const SplitOperator& op) {
+  int w = 0;
+  for (int i = 0; i < op.ell; ++i) {
+    if (op.is_diag[i]) continue;
+    if (op.is_cplx[i] || op.band_w[i] == 0 || op.band_w[i] > kNarrowMax) return 0;
+    w = std::max(w, op.band_w[i]);
+  }
+  return band_class(w);
+}
+
 nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, hipStream_t st) {
   // Z blocks of the low-rank terms of real problems (the complex-term
   // residual multiplies every term densely)
@@ -285,6 +299,9 @@ nep_status MomentsPlan::rebind_members(const std::vector<int>& member, const std
 }
 
 void MomentsPlan::release_fallback() {
+  dF64_.release();
+  dpiv64_.release();
+  dpmin64_.release();
   dT64_.release();
   ddinv64_.release();
   dlinv64_.release();
@@ -297,7 +314,8 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   hpd_.assign(nprob, ProbDesc{});
   std::vector<int> hprob, hj;
   std::vector<MatDesc> all;
-  long long offT = 0, offW = 0, offY = 0;
+  std::vector<MatDesc> dense;
+  long long offT = 0, offW = 0, offY = 0, offF = 0, offP = 0;
   int offRow = 0, g = 0;
   for (int p = 0; p < nprob; ++p) {
     const int n = probs[p].op->n;
@@ -313,6 +331,9 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     D.offW0 = offW;
     D.offY = offY;
     D.offRow0 = offRow;
+    D.band = o.dense ? 0 : band_of(*probs[p].op);
+    D.offF = offF;
+    D.offP = offP;
     for (int j = 0; j < o.N; ++j, ++g) {
       MatDesc m;
       m.n = n;
@@ -321,10 +342,16 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
       m.offRow = offRow + j * n;
       m.node = g;
       all.push_back(m);
+      if (!D.band) dense.push_back(m);
       hprob.push_back(p);
       hj.push_back(j);
     }
-    offT += (long long)o.N * D.strideT;
+    if (D.band) {
+      offF += (long long)o.N * n * band_entries(D.band);
+      offP += (long long)o.N * n;
+    } else {
+      offT += (long long)o.N * D.strideT;
+    }
     offW += (long long)o.N * n * o.L;
     offY += (long long)n * o.N * o.L;
     offRow += o.N * n;
@@ -334,8 +361,13 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   w_elems_ = offW;
   y_elems_ = offY;
   rows_total_ = offRow;
-  sorted_ = all;
-  std::stable_sort(sorted_.begin(), sorted_.end(), [](const MatDesc& a, const MatDesc& b) { return a.n > b.n; });
+  f_elems_ = offF;
+  any_band_ = offF > 0;
+  const auto larger = [](const MatDesc& a, const MatDesc& b) { return a.n > b.n; };
+  sorted_ = dense;
+  std::stable_sort(sorted_.begin(), sorted_.end(), larger);
+  shapes_ = all;
+  std::stable_sort(shapes_.begin(), shapes_.end(), larger);
 
   lu_.build(sorted_, o.prec);
   const bool mixed = o.prec == NEP_PREC_C32_IR64;
@@ -348,22 +380,23 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     // two groups (they halve the operand traffic per product)
     long long big_tiles = 0;
     for (int p = 0; p < nprob; ++p)
-      if (probs[p].op->a_cplx == 0)
+      if (probs[p].op->a_cplx == 0 && !hpd_[p].band)
         big_tiles += (long long)ceil_div(hpd_[p].n, kResidBigTM) * ceil_div(2 * o.N * o.L, kResidBigTQ);
     pt_.resid_big = big_tiles >= 512 ? 1 : 0;
     const int rtm = pt_.resid_big ? kResidBigTM : kResidRealTM, rtq = pt_.resid_big ? kResidBigTQ : kResidRealTQ;
     for (int p = 0; p < nprob; ++p) {
       const long long n = hpd_[p].n;
-      const bool cplx = probs[p].op->a_cplx != 0;
-      ca.push_back((int)ceil_div_ll(n * n, 256));
-      cr.push_back(cplx ? ceil_div((int)n, 64) * ceil_div(2 * o.N * o.L, 64) : 0);
-      crr.push_back(cplx ? 0 : ceil_div((int)n, rtm) * ceil_div(2 * o.N * o.L, rtq));
+      const bool cplx = probs[p].op->a_cplx != 0, band = hpd_[p].band != 0;
+      ca.push_back(band ? 0 : (int)ceil_div_ll(n * n, 256));
+      cr.push_back(band ? 0 : cplx ? ceil_div((int)n, 64) * ceil_div(2 * o.N * o.L, 64) : 0);
+      crr.push_back(band || cplx ? 0 : ceil_div((int)n, rtm) * ceil_div(2 * o.N * o.L, rtq));
       cm.push_back(ceil_div((int)n * o.L, 256) * ceil_div(2 * o.K, 8));  // (row, column) blocks x moment groups
     }
     build_prefix(hprefix_, pt_.assemble, ca);
     build_prefix(hprefix_, pt_.resid, cr);
     build_prefix(hprefix_, pt_.resid_real, crr);
     build_prefix(hprefix_, pt_.moments, cm);
+    band_tables(bt_, hprefix_, hpd_);
   }
 
   const size_t es = elem_size(o.prec);
@@ -378,6 +411,9 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_TRY(A(dprefix_, sizeof(int) * hprefix_.size()));
   NEP_TRY(A(dlu_prefix_, sizeof(int) * std::max<size_t>(1, lu_.prefix.size())));
   NEP_TRY(A(dT_, es * (size_t)t_elems_));
+  NEP_TRY(A(dF_, es * (size_t)f_elems_));
+  NEP_TRY(A(dpiv_, (size_t)offP));
+  NEP_TRY(A(dpmin_, any_band_ ? sizeof(double) * (size_t)nnodes : 0));
   if (sp_.nblk > 0) {  // right-hand sides of the blocked solve
     NEP_TRY(A(dW_, sizeof(c64) * (size_t)sp_.nblk * sp_.npad * sp_.L));
     sp_.W = dW_.as<c64>();
@@ -398,7 +434,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_TRY(A(dlinv_, 2 * es * (size_t)sorted_.size() * kLuMaxJB * kLuMaxJB));
   NEP_TRY(A(darrive_, sizeof(int) * std::max<size_t>(1, sorted_.size())));
   NEP_HIP(hipMemsetAsync(darrive_.p, 0, sizeof(int) * std::max<size_t>(1, sorted_.size()), st));
-  NEP_TRY(A(ddinv_off_, sizeof(long long) * dinv_off_.size()));
+  NEP_TRY(A(ddinv_off_, sizeof(long long) * std::max<size_t>(1, dinv_off_.size())));
   NEP_TRY(A(dY_, sizeof(c128) * (size_t)y_elems_));
   NEP_TRY(A(dR_, sizeof(c128) * (size_t)y_elems_));
   const size_t G = nnodes;
@@ -448,19 +484,19 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   }
 
   // pageable sources: each copy has taken its bytes when the call returns
-  NEP_HIP(hipMemcpyAsync(dmd_.p, sorted_.data(), sizeof(MatDesc) * sorted_.size(), hipMemcpyHostToDevice, st));
+  if (!sorted_.empty()) {
+    NEP_HIP(hipMemcpyAsync(dmd_.p, sorted_.data(), sizeof(MatDesc) * sorted_.size(), hipMemcpyHostToDevice, st));
+    NEP_HIP(hipMemcpyAsync(ddinv_off_.p, dinv_off_.data(), sizeof(long long) * dinv_off_.size(),
+                           hipMemcpyHostToDevice, st));
+  }
   NEP_HIP(hipMemcpyAsync(dprefix_.p, hprefix_.data(), sizeof(int) * hprefix_.size(), hipMemcpyHostToDevice, st));
   if (!lu_.prefix.empty())
     NEP_HIP(hipMemcpyAsync(dlu_prefix_.p, lu_.prefix.data(), sizeof(int) * lu_.prefix.size(),
                            hipMemcpyHostToDevice, st));
-  NEP_HIP(hipMemcpyAsync(ddinv_off_.p, dinv_off_.data(), sizeof(long long) * dinv_off_.size(),
-                         hipMemcpyHostToDevice, st));
   NEP_HIP(hipMemcpyAsync(na_.prob, hprob.data(), sizeof(int) * G, hipMemcpyHostToDevice, st));
   na_prob_host_ = hprob;
   NEP_HIP(hipMemcpyAsync(na_.jnode, hj.data(), sizeof(int) * G, hipMemcpyHostToDevice, st));
-  dT64_.release();
-  ddinv64_.release();
-  dlinv64_.release();
+  release_fallback();
   return upload_problems(probs, st);
 }
 
@@ -474,6 +510,7 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   c128* R = dR_.as<c128>();
   int* rows = drows_.as<int>();
   int* info = dinfo_.as<int>();
+  unsigned char* piv = dpiv_.as<unsigned char>();
   NEP_HIP(ir_reset(ir_, nnodes, st));
   NEP_HIP(launch_coef(pd, na_, nnodes, ir_, st));
   if (refactor) NEP_HIP(launch_assemble<P>(pd, pre, pt_.assemble, na_, T, nullptr, st));
@@ -486,6 +523,8 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
     if (eager) NEP_HIP(hipEventRecord(ev_lu_[0], st));
     NEP_HIP(lu_run<P>(lu_, md, dlu_prefix_.as<int>(), T, rows, drows_snap_.as<int>(), rows_total_, info, nullptr,
                       dlinv_.as<cx<P>>(), Dinv, doff, darrive_.as<int>(), st, ls_));
+    if (any_band_)
+      NEP_HIP(band_factor<P>(bt_, pd, pre, na_, dF_.as<cx<P>>(), piv, info, dpmin_.as<double>(), nullptr, st));
     if (eager) {
       NEP_HIP(hipEventRecord(ev_lu_[1], st));
       lu_timed_ = true;
@@ -493,6 +532,7 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   }
   // nodes of problems sitting out the pass are marked converged by k_coef
   NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, nullptr, Y, false, ir_.conv, ir_, st));
+  if (any_band_) NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, kBandV, ir_.conv, ir_, st));
   sweeps_run_ = 0;
   if (opt.max_refine > 0) {
     // The correction solve of each sweep is queued before the host reads the
@@ -502,14 +542,17 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
     for (int s = 0; s <= opt.max_refine; ++s) {
       NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, Y, R, ir_, nnodes, st,
                         lr_jobs_.data(), (int)lr_jobs_.size()));
+      if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, Y, R, ir_, st));
       NEP_HIP(ir_control(pd, na_, ir_, nnodes, s, opt.tol, st));
       sweeps_run_ = s;
       if (eager) {
         NEP_HIP(hipMemcpyAsync(hcounter_, ir_.counters, sizeof(int), hipMemcpyDeviceToHost, st));
         NEP_HIP(hipEventRecord(ev_counter_, st));
       }
-      if (s < opt.max_refine)
+      if (s < opt.max_refine) {
         NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, R, Y, true, ir_.conv, ir_, st));
+        if (any_band_) NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, kBandRefine, ir_.conv, ir_, st));
+      }
       if (eager) {
         NEP_HIP(hipEventSynchronize(ev_counter_));
         if (hcounter_[0] == 0) break;
@@ -529,15 +572,21 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
 template <typename P>
 nep_status MomentsPlan::run_fallback(hipStream_t st) {
   static_assert(sizeof(P) == 8, "fallback runs in FP64");
-  if (!dT64_.p) {
+  if (!dT64_.p && !dF64_.p) {
     auto alloc64 = [&]() -> nep_status {
       nep_status s = dT64_.alloc(sizeof(c128) * (size_t)t_elems_);
       if (s == NEP_OK) s = ddinv64_.alloc(sizeof(c128) * (size_t)dinv_elems_);
       if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted_.size() * kLuMaxJB * kLuMaxJB);
+      if (s == NEP_OK) s = dF64_.alloc(sizeof(c128) * (size_t)f_elems_);
+      if (s == NEP_OK) s = dpiv64_.alloc(dpiv_.bytes);
+      if (s == NEP_OK) s = dpmin64_.alloc(dpmin_.bytes);
       if (s != NEP_OK) {
         dT64_.release();
         ddinv64_.release();
         dlinv64_.release();
+        dF64_.release();
+        dpiv64_.release();
+        dpmin64_.release();
       }
       return s;
     };
@@ -597,11 +646,20 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
       NEP_HIP(hipStreamSynchronize(st));  // the compact tables leave scope
     }
   }
+  // band problems: their unconverged nodes in FP64, over the band again
+  unsigned char* piv = dpiv64_.as<unsigned char>();
+  if (any_band_)
+    NEP_HIP(band_factor<double>(bt_, pd, pre, na_, dF64_.as<c128>(), piv, dinfo_.as<int>(), dpmin64_.as<double>(),
+                                skip, st));
   NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
                             skip, ir_, st));
+  if (any_band_)
+    NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandV, skip, ir_,
+                               st));
   for (int s = 0;; ++s) {
     NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, dY_.as<c128>(), dR_.as<c128>(), ir_, nnodes, st,
                       lr_jobs_.data(), (int)lr_jobs_.size()));
+    if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, dY_.as<c128>(), dR_.as<c128>(), ir_, st));
     NEP_HIP(ir_control(pd, na_, ir_, nnodes, opt.max_refine + 1 + s, opt.tol, st));
     if (s == kFallbackSweeps) break;
     NEP_HIP(hipMemcpyAsync(hcounter_, ir_.counters, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -609,6 +667,9 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     if (hcounter_[0] == 0) break;
     NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
                               true, ir_.conv, ir_, st));
+    if (any_band_)
+      NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandRefine, ir_.conv,
+                                 ir_, st));
   }
   fallback_pending_ = true;
   return NEP_OK;
@@ -623,6 +684,9 @@ nep_status MomentsPlan::factor_t(hipStream_t st) {
   NEP_HIP(lu_run<P>(lu_, dmd_.as<MatDesc>(), dlu_prefix_.as<int>(), dT_.as<cx<P>>(), drows_.as<int>(),
                     drows_snap_.as<int>(), rows_total_, dinfo_.as<int>(), nullptr, dlinv_.as<cx<P>>(),
                     ddinv_.as<cx<P>>(), ddinv_off_.as<long long>(), darrive_.as<int>(), st, ls_));
+  if (any_band_)
+    NEP_HIP(band_factor<P>(bt_, pd, dprefix_.as<int>(), na_, dF_.as<cx<P>>(), dpiv_.as<unsigned char>(),
+                           dinfo_.as<int>(), dpmin_.as<double>(), nullptr, st));
   return NEP_OK;
 }
 
@@ -632,6 +696,9 @@ nep_status MomentsPlan::solve_rhs_t(hipStream_t st) {
   NEP_HIP(solve_run<P>(sp_, dpd_.as<ProbDesc>(), dmd_.as<MatDesc>(), na_, dT_.as<cx<P>>(), drows_.as<int>(),
                        ddinv_.as<cx<P>>(), ddinv_off_.as<long long>(), dR_.as<c128>(), dY_.as<c128>(), true,
                        nullptr, ir_, st));
+  if (any_band_)
+    NEP_HIP(band_solve<P>(bt_, dpd_.as<ProbDesc>(), dprefix_.as<int>(), dF_.as<cx<P>>(), dpiv_.as<unsigned char>(),
+                          dR_.as<c128>(), dY_.as<c128>(), kBandR, nullptr, ir_, st));
   return NEP_OK;
 }
 
@@ -652,17 +719,26 @@ nep_status MomentsPlan::enqueue(hipStream_t st, bool eager, bool refactor) {
 }
 
 template <typename P>
-hipError_t logdet_run(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, double* out, hipStream_t st);
+hipError_t logdet_run(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, int nnodes, double* out,
+                      hipStream_t st);
 
 nep_status MomentsPlan::logdet(hipStream_t st, std::vector<double>& logabs, std::vector<double>& arg) {
   DevMem out;
   NEP_TRY(out.alloc(sizeof(double) * 2 * (size_t)nnodes));
   if (opt.prec == NEP_PREC_FP64)
     NEP_HIP(logdet_run<double>(dmd_.as<MatDesc>(), (int)sorted_.size(), dT_.as<c128>(), drows_.as<int>(),
-                               out.as<double>(), st));
+                               nnodes, out.as<double>(), st));
   else
     NEP_HIP(logdet_run<float>(dmd_.as<MatDesc>(), (int)sorted_.size(), dT_.as<c64>(), drows_.as<int>(),
-                              out.as<double>(), st));
+                              nnodes, out.as<double>(), st));
+  if (any_band_) {
+    const ProbDesc* pd = dpd_.as<ProbDesc>();
+    const unsigned char* piv = dpiv_.as<unsigned char>();
+    if (opt.prec == NEP_PREC_FP64)
+      NEP_HIP(band_logdet<double>(bt_, pd, dprefix_.as<int>(), dF_.as<c128>(), piv, nnodes, out.as<double>(), st));
+    else
+      NEP_HIP(band_logdet<float>(bt_, pd, dprefix_.as<int>(), dF_.as<c64>(), piv, nnodes, out.as<double>(), st));
+  }
   std::vector<double> h(2 * (size_t)nnodes);
   NEP_HIP(hipMemcpyAsync(h.data(), out.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
   NEP_HIP(hipStreamSynchronize(st));
@@ -677,7 +753,7 @@ nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallba
   std::vector<double> rho(G);
   std::vector<double> pmin(G);
   auto read_back = [&]() -> nep_status {  // one gathered block, one copy
-    NEP_HIP(gather_status(ir_, dinfo_.as<int>(), na_.bad, G, dstat_.p, st));
+    NEP_HIP(gather_status(ir_, dinfo_.as<int>(), na_.bad, dpmin_.as<double>(), G, dstat_.p, st));
     if (opt.prec == NEP_PREC_FP64)
       NEP_HIP(min_pivot<double>(dmd_.as<MatDesc>(), (int)sorted_.size(), dT_.as<c128>(), drows_.as<int>(), G,
                                 dstat_.p, st));

@@ -106,6 +106,7 @@ struct PlanOptions {
   int N = 32, L = 8, K = 2, prec = NEP_PREC_C32_IR64;
   int max_refine = 5, fallback = 1;
   double tol = kDefaultRefineTol;
+  bool dense = false;  // dense factors whatever the terms' structure (callers that read the factors themselves)
 };
 
 struct RunResult {
@@ -231,11 +232,16 @@ class MomentsPlan {
   std::vector<LrJob> lr_jobs_;  // low-rank terms of real problems (Z = H^T Y per residual)
   DevMem dlrz_;                 // their Z blocks
   DevMem dlrzp_;                // partial sums of one Z block (the jobs run in turn on one stream)
-  std::vector<MatDesc> sorted_;
+  std::vector<MatDesc> sorted_;  // the matrices with dense factors, largest first
+  std::vector<MatDesc> shapes_;  // every matrix, largest first (identifies and tunes the plan)
   std::vector<int> prob_of_sorted_;
   LuPlan lu_;
   SolvePlan sp_;
   ProblemTables pt_;
+  BandTables bt_;                     // band problems (band.hip)
+  bool any_band_ = false;
+  DevMem dF_, dF64_, dpiv_, dpiv64_, dpmin_, dpmin64_;   // their factors, pivots and smallest pivot moduli
+  long long f_elems_ = 0;
   std::vector<int> hprefix_;
   DevMem dpd_, dmd_, dprefix_, dlu_prefix_;
   DevMem dT_, drows_, drows_snap_, dinfo_, dY_, dR_, dnode_, dir_, dT64_, dW_;

@@ -526,13 +526,14 @@ hipError_t ir_control(const ProbDesc* pd, const NodeArrays& na, IrState ir, int 
 // Per-node status for the host in one block (one copy instead of one per
 // array): rho[G] and the smallest pivot modulus pmin[G] (double), then info,
 // conv, sweeps, bad (int each), then the four counters.
-__global__ void k_gather_status(IrState ir, const int* __restrict__ info, const int* __restrict__ bad, int G,
-                                char* __restrict__ out) {
+__global__ void k_gather_status(IrState ir, const int* __restrict__ info, const int* __restrict__ bad,
+                                const double* __restrict__ pmin, int G, char* __restrict__ out) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   double* rho = reinterpret_cast<double*>(out);
   int* iv = reinterpret_cast<int*>(out + 2 * (size_t)G * sizeof(double));
   if (g < G) {
     rho[g] = ir.rho[g];
+    if (pmin != nullptr) rho[G + g] = pmin[g];
     iv[g] = info[g];
     iv[G + g] = ir.conv[g];
     iv[2 * G + g] = ir.sweeps[g];
@@ -572,6 +573,7 @@ __global__ __launch_bounds__(256) void k_min_pivot(const MatDesc* __restrict__ m
 template <typename P>
 hipError_t min_pivot(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, int G, void* status,
                      hipStream_t st) {
+  if (nmat == 0) return hipSuccess;
   double* out = reinterpret_cast<double*>(static_cast<char*>(status) + (size_t)G * sizeof(double));
   hipLaunchKernelGGL(k_min_pivot<P>, dim3(nmat), dim3(256), 0, st, md, T, rows, out);
   return hipGetLastError();
@@ -632,16 +634,19 @@ __global__ __launch_bounds__(256) void k_logdet(const MatDesc* __restrict__ md, 
 }
 
 template <typename P>
-hipError_t logdet_run(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_logdet<P>, dim3(nmat), dim3(256), 0, st, md, T, rows, nmat, out);
+hipError_t logdet_run(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, int nnodes, double* out,
+                      hipStream_t st) {
+  if (nmat == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_logdet<P>, dim3(nmat), dim3(256), 0, st, md, T, rows, nnodes, out);
   return hipGetLastError();
 }
-template hipError_t logdet_run<float>(const MatDesc*, int, const c64*, const int*, double*, hipStream_t);
-template hipError_t logdet_run<double>(const MatDesc*, int, const c128*, const int*, double*, hipStream_t);
+template hipError_t logdet_run<float>(const MatDesc*, int, const c64*, const int*, int, double*, hipStream_t);
+template hipError_t logdet_run<double>(const MatDesc*, int, const c128*, const int*, int, double*, hipStream_t);
 template hipError_t min_pivot<double>(const MatDesc*, int, const c128*, const int*, int, void*, hipStream_t);
 
-hipError_t gather_status(IrState ir, const int* info, const int* bad, int G, void* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_status, dim3(ceil_div(std::max(G, 4), 256)), dim3(256), 0, st, ir, info, bad, G,
+hipError_t gather_status(IrState ir, const int* info, const int* bad, const double* pmin, int G, void* out,
+                         hipStream_t st) {
+  hipLaunchKernelGGL(k_gather_status, dim3(ceil_div(std::max(G, 4), 256)), dim3(256), 0, st, ir, info, bad, pmin, G,
                      static_cast<char*>(out));
   return hipGetLastError();
 }

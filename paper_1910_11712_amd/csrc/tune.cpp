@@ -83,6 +83,12 @@ nep_status MomentsPlan::apply(const Knobs& k, hipStream_t st) {
 
 void MomentsPlan::candidates(std::vector<Knobs>& lu, std::vector<Knobs>& solve) const {
   const Knobs base = knobs();
+  // the shapes of every matrix: a plan of band problems alone lists the same
+  // settings (its launches do not depend on them)
+  LuPlan all;
+  all.build(shapes_, opt.prec, base.jb);
+  const std::vector<MatDesc>& sorted_ = shapes_;
+  const LuPlan& lu_ = all;
   lu.assign(1, base);
   solve.assign(1, base);
   const bool f32 = opt.prec == NEP_PREC_C32_IR64;
@@ -140,13 +146,13 @@ void MomentsPlan::candidates(std::vector<Knobs>& lu, std::vector<Knobs>& solve) 
 
 std::string MomentsPlan::signature() const {
   std::uint64_t h = 1469598103934665603ull;  // FNV-1a over the sorted sizes
-  for (const auto& m : sorted_) {
+  for (const auto& m : shapes_) {
     h ^= (std::uint64_t)m.n;
     h *= 1099511628211ull;
   }
   char buf[160];
-  std::snprintf(buf, sizeof buf, "prec%d N%d L%d sweeps%d fb%d m%zu sizes%016llx", opt.prec, opt.N, opt.L,
-                opt.max_refine, opt.fallback, sorted_.size(), (unsigned long long)h);
+  std::snprintf(buf, sizeof buf, "prec%d N%d L%d sweeps%d fb%d m%zu dense%zu sizes%016llx", opt.prec, opt.N, opt.L,
+                opt.max_refine, opt.fallback, shapes_.size(), sorted_.size(), (unsigned long long)h);
   return buf;
 }
 
