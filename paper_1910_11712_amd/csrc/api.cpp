@@ -132,9 +132,24 @@ static int detect_low_rank(int n, const double* h, long long ld, int rmax, std::
       }
     }
   });
-  // Householder QR of Y (n x k), reflectors kept in place
+  // Householder QR of Y (n x k) with column pivoting, reflectors kept in place.
+  // The first r columns of Y alone are a random r x r mixture of A's range,
+  // now and then ill-conditioned enough to spoil Q_r beyond the check below;
+  // the r columns that pivoting picks out of r + 8 or more are not.
   std::vector<double> tau(k, 0.0), diag(k, 0.0);
   for (int j = 0; j < k; ++j) {
+    int best = j;
+    double top = -1.0;
+    for (int jj = j; jj < k; ++jj) {
+      const double* y = &Y[(size_t)jj * n];
+      double s = 0.0;
+      for (int r = j; r < n; ++r) s += y[r] * y[r];
+      if (s > top) {
+        top = s;
+        best = jj;
+      }
+    }
+    if (best != j) std::swap_ranges(&Y[(size_t)j * n], &Y[(size_t)j * n] + n, &Y[(size_t)best * n]);
     double* x = &Y[(size_t)j * n];
     double s2 = 0.0;
     for (int r = j + 1; r < n; ++r) s2 += x[r] * x[r];

@@ -54,7 +54,7 @@ struct ProbDesc {
   int a_bw[kMaxTerms];             // real banded A_i (half-bandwidth, 0: not banded): the
                                    // real-term residual runs over the band's k only
   int a_lr[kMaxTerms];             // real low-rank A_i = G H^T (rank, 0: not factored):
-  const double* LrG[kMaxTerms];    // the real-term residual applies G (H^T Y), with
+  const double *LrG[kMaxTerms], *LrH[kMaxTerms];  // the real-term residual applies G (H^T Y), with
   c128* LrZ[kMaxTerms];            // Z = H^T Y (rank x N*L) formed before it
   const c128* V;          // caller probes, column-major n x L
   c128* S;                // caller moments, column-major n x L x KK
@@ -64,6 +64,7 @@ struct ProbDesc {
   int active;             // 0: the problem sits out this pass on resident factors (its
                           // nodes count as converged, its V and S are not touched)
   int band;               // 0: dense factors; else the band path's window half-width (1, 2 or 4)
+  int bordered;           // 1: takes the bordered path
   long long offF, offP;   // its factor (elements) and pivot bytes
   const c128* fpts;       // with zpts: given coefficients in place of f_i(z_j), at
                           // fpts[j*ell + i] (device), or nullptr
@@ -126,6 +127,7 @@ void solve_set_lg(SolvePlan& sp, int lg, int L);
 
 struct ProblemTables {
   Table assemble;  // element tiles per problem
+  Table assemble64;  // the same for an FP64 re-solve (bordered problems too)
   Table resid;       // residual GEMM tiles per problem with complex terms (64 x 64)
   Table resid_real;  // residual GEMM tiles per problem with real terms only (kResidRealTM x kResidRealTQ,
                      // or kResidBigTM x kResidBigTQ with resid_big)
@@ -160,6 +162,43 @@ hipError_t band_resid(const BandTables& bt, const ProbDesc* pd, const int* prefi
 template <typename P>
 hipError_t band_logdet(const BandTables& bt, const ProbDesc* pd, const int* prefix, const cx<P>* F,
                        const unsigned char* piv, int nnodes, double* out, hipStream_t st);
+
+// The bordered path (border.hip): one descriptor per problem that takes it.
+constexpr int kBdBlk = 32;                            // block rows, and the widest band
+constexpr int kBdMaxBlocks = (4096 + kBdBlk - 1) / kBdBlk;
+constexpr int kBdMinN = 256, kBdMinRatio = 4;         // matrix size, and its ratio to the border's, from which it is taken
+constexpr int kBdMaxRank = 256;                       // sum of the low-rank terms' ranks
+struct BdProb {
+  int prob, w, nb, nch;          // problem, half-width, blocks, chunks
+  int rp, wc, Lp, pw, b;         // low-rank columns (padded to blocks), columns of W, of X, of a partial
+                                 // product, size of the border
+  int ldS, offRowS;
+  long long strideS;
+  // element offsets: chunk factors, W, X, partial products, row orders (bytes), pivots, F blocks, border
+  // matrix, border right-hand sides
+  long long offB, offW, offX, offPart, offPerm, offPiv, offFB, offS, offYS;
+};
+struct BdBufs {
+  c64 *blocks, *W, *X, *part, *pivots, *FB, *S;
+  unsigned char* perms;
+  c128 *RS, *YS;
+};
+struct BdTables {
+  Table lu, solve_e, solve_v, hprod_e, hprod_v, border, rhs, apply, node;
+};
+void bd_tables(BdTables& bt, std::vector<int>& buf, const std::vector<BdProb>& bp, const std::vector<ProbDesc>& pd);
+// chunk factors, W and the border matrices (their LU follows)
+hipError_t bd_factor(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const NodeArrays& na,
+                     const BdBufs& m, int* info, hipStream_t st);
+// a solve up to the border's right-hand sides RS (YS cleared), and, with YS solved for, from there on:
+// Y = T^{-1} V, or (refine) Y += T^{-1} R
+hipError_t bd_solve_pre(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const NodeArrays& na,
+                        const BdBufs& m, const c128* R, bool refine, const int* conv, hipStream_t st);
+hipError_t bd_solve_post(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const BdBufs& m,
+                         c128* Y, bool refine, const int* conv, IrState ir, hipStream_t st);
+// smallest pivot moduli, and (det not null) log|det T| and arg det T as logdet_run, of the bordered problems
+hipError_t bd_pivots(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const BdBufs& m,
+                     const int* rowsS, double* pmin, double* det, int nnodes, hipStream_t st);
 
 // Kernel launchers (all asynchronous on st).
 hipError_t launch_coef(const ProbDesc* pd, const NodeArrays& na, int nnodes, IrState ir, hipStream_t st);

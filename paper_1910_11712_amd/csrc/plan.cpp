@@ -198,6 +198,154 @@ static int band_of(const SplitOperator& op) {
   return band_class(w);
 }
 
+// Half-width of the bordered path when every term of the operator is real and
+// diagonal, banded with a half-width of at most kBdBlk, or low-rank; -1: not
+// so, or the dense path is as good: the border (its chunks' separators and the
+// low-rank columns) has to be small beside the matrix.
+static int bordered_of(const SplitOperator& op, int& rank, int& nch) {
+  int w = 0;
+  rank = 0;
+  if (op.a_cplx) return -1;  // (low-rank terms are kept factored for real problems only)
+  for (int i = 0; i < op.ell; ++i) {
+    if (op.is_diag[i]) continue;
+    if (op.lr_rank[i] > 0) rank += op.lr_rank[i];
+    else if (op.band_w[i] >= 1 && op.band_w[i] <= kBdBlk) w = std::max(w, op.band_w[i]);
+    else return -1;
+  }
+  if (rank > kBdMaxRank) return -1;
+  const int nb = ceil_div(op.n, kBdBlk);
+  nch = std::min(4, std::max(1, nb / 16));
+  const int b = (nch - 1) * kBdBlk + ceil_div(rank, kBdBlk) * kBdBlk;
+  return op.n >= std::max(kBdMinN, kBdMinRatio * b) ? w : -1;
+}
+
+nep_status MomentsPlan::build_bordered(const std::vector<PlanProblem>& probs) {
+  bp_.clear();
+  hpdb_.assign(nprob, ProbDesc{});
+  sortedb_.clear();
+  rowsb_total_ = 0;
+  long long oB = 0, oW = 0, oX = 0, oP = 0, oM = 0, oV = 0, oF = 0, oS = 0, oY = 0;
+  for (int p = 0; p < nprob; ++p) {
+    ProbDesc& D = hpd_[p];
+    if (!D.bordered) continue;
+    BdProb q{};
+    int rank;
+    q.prob = p;
+    q.w = bordered_of(*probs[p].op, rank, q.nch);
+    q.nb = ceil_div(D.n, kBdBlk);
+    q.rp = ceil_div(rank, kBdBlk) * kBdBlk;
+    q.wc = 2 * kBdBlk + q.rp;
+    q.Lp = ceil_div(D.L, kBdBlk) * kBdBlk;
+    q.pw = std::max(q.wc, q.Lp);
+    q.b = (q.nch - 1) * kBdBlk + q.rp;
+    q.ldS = pad_ld(std::max(1, q.b));
+    q.strideS = (long long)q.ldS * q.b;
+    q.offRowS = rowsb_total_;
+    const long long N = D.N, bl2 = kBdBlk * kBdBlk;
+    q.offB = oB;
+    q.offW = oW;
+    q.offX = oX;
+    q.offPart = oP;
+    q.offPerm = oM;
+    q.offPiv = oV;
+    q.offFB = oF;
+    q.offS = oS;
+    q.offYS = oY;
+    oB += N * q.nb * 5 * bl2;
+    oW += N * q.nb * kBdBlk * q.wc;
+    oX += N * q.nb * kBdBlk * q.Lp;
+    oP += N * q.nch * q.rp * q.pw;
+    oM += N * q.nb * 2 * kBdBlk;
+    oV += N * q.nb * kBdBlk;
+    oF += N * (q.nch - 1) * 2 * bl2;
+    oS += N * q.strideS;
+    oY += (long long)q.b * N * D.L;
+    ProbDesc& E = hpdb_[p];
+    E.n = q.b;
+    E.N = D.N;
+    E.L = D.L;
+    E.node0 = D.node0;
+    E.offY = q.offYS;
+    if (q.b > 0)
+      for (int j = 0; j < D.N; ++j)
+        sortedb_.push_back(MatDesc{q.b, q.ldS, q.offS + j * q.strideS, q.offRowS + j * q.b, D.node0 + j});
+    rowsb_total_ += D.N * q.b;
+    bp_.push_back(q);
+  }
+  if (bp_.empty()) return NEP_OK;
+  std::stable_sort(sortedb_.begin(), sortedb_.end(), [](const MatDesc& a, const MatDesc& b) { return a.n > b.n; });
+  lub_.build(sortedb_, opt.prec);
+  SolvePlan_build(spb_, hprefix_, sortedb_, opt.L, opt.prec, dinvb_off_, dinvb_elems_);
+  bd_tables(bdt_, hprefix_, bp_, hpd_);
+  const size_t c8 = sizeof(c64), c16 = sizeof(c128);
+  const size_t sizes[10] = {c8 * oB, c8 * oW, c8 * oX, c8 * oP, c8 * oV, c8 * oF, c8 * oS, (size_t)oM, c16 * oY, c16 * oY};
+  auto A = [&](DevMem& m, size_t b) -> nep_status {
+    total_bytes_ += b;
+    return m.alloc(b);
+  };
+  for (int i = 0; i < 10; ++i) NEP_TRY(A(dbd_[i], sizes[i]));
+  bd_ = BdBufs{dbd_[0].as<c64>(), dbd_[1].as<c64>(), dbd_[2].as<c64>(), dbd_[3].as<c64>(), dbd_[4].as<c64>(),
+               dbd_[5].as<c64>(), dbd_[6].as<c64>(), dbd_[7].as<unsigned char>(), dbd_[8].as<c128>(),
+               dbd_[9].as<c128>()};
+  const size_t m = std::max<size_t>(1, sortedb_.size());
+  NEP_TRY(A(dbp_, sizeof(BdProb) * bp_.size()));
+  NEP_TRY(A(dpdb_, sizeof(ProbDesc) * nprob));
+  NEP_TRY(A(dmdb_, sizeof(MatDesc) * m));
+  NEP_TRY(A(dlub_prefix_, sizeof(int) * std::max<size_t>(1, lub_.prefix.size())));
+  NEP_TRY(A(drowsb_, sizeof(int) * std::max(1, rowsb_total_)));
+  NEP_TRY(A(drowsb_snap_, sizeof(int) * std::max(1, rowsb_total_)));
+  NEP_TRY(A(dinfob_, sizeof(int) * (size_t)nnodes));
+  NEP_TRY(A(ddinvb_, c8 * (size_t)std::max(1ll, dinvb_elems_)));
+  NEP_TRY(A(ddinvb_off_, sizeof(long long) * m));
+  NEP_TRY(A(dlinvb_, 2 * c8 * m * kLuMaxJB * kLuMaxJB));
+  NEP_TRY(A(darriveb_, sizeof(int) * m));
+  NEP_TRY(A(dynormb_, 8 * (size_t)nnodes * kNormStride));
+  NEP_CHECK(spb_.nblk == 0, NEP_ERR_ARG, "border larger than the batched solve's per-node range");
+  return NEP_OK;
+}
+
+nep_status MomentsPlan::upload_bordered(hipStream_t st) {
+  if (bp_.empty()) return NEP_OK;
+  NEP_HIP(hipMemcpyAsync(dbp_.p, bp_.data(), sizeof(BdProb) * bp_.size(), hipMemcpyHostToDevice, st));
+  NEP_HIP(hipMemcpyAsync(dpdb_.p, hpdb_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
+  NEP_HIP(hipMemsetAsync(darriveb_.p, 0, darriveb_.bytes, st));
+  NEP_HIP(hipMemsetAsync(dynormb_.p, 0, dynormb_.bytes, st));
+  if (sortedb_.empty()) return NEP_OK;
+  NEP_HIP(hipMemcpyAsync(dmdb_.p, sortedb_.data(), sizeof(MatDesc) * sortedb_.size(), hipMemcpyHostToDevice, st));
+  NEP_HIP(hipMemcpyAsync(ddinvb_off_.p, dinvb_off_.data(), sizeof(long long) * dinvb_off_.size(),
+                         hipMemcpyHostToDevice, st));
+  if (!lub_.prefix.empty())
+    NEP_HIP(hipMemcpyAsync(dlub_prefix_.p, lub_.prefix.data(), sizeof(int) * lub_.prefix.size(),
+                           hipMemcpyHostToDevice, st));
+  return NEP_OK;
+}
+
+nep_status MomentsPlan::bordered_factor(hipStream_t st) {
+  const ProbDesc* pd = dpd_.as<ProbDesc>();
+  const int* pre = dprefix_.as<int>();
+  NEP_HIP(bd_factor(bdt_, dbp_.as<BdProb>(), pd, pre, na_, bd_, dinfo_.as<int>(), st));
+  NEP_HIP(lu_run<float>(lub_, dmdb_.as<MatDesc>(), dlub_prefix_.as<int>(), bd_.S, drowsb_.as<int>(),
+                        drowsb_snap_.as<int>(), rowsb_total_, dinfob_.as<int>(), nullptr, dlinvb_.as<c64>(),
+                        ddinvb_.as<c64>(), ddinvb_off_.as<long long>(), darriveb_.as<int>(), st,
+                        st == beside_ ? LuStreams{} : ls_));  // (ls_ belongs to the dense LU there)
+  NEP_HIP(bd_pivots(bdt_, dbp_.as<BdProb>(), pd, pre, bd_, drowsb_.as<int>(), dpmin_.as<double>(), nullptr, nnodes,
+                    st));
+  return NEP_OK;
+}
+
+nep_status MomentsPlan::bordered_solve(bool refine, hipStream_t st) {
+  const ProbDesc* pd = dpd_.as<ProbDesc>();
+  const BdProb* bp = dbp_.as<BdProb>();
+  const int* pre = dprefix_.as<int>();
+  NEP_HIP(bd_solve_pre(bdt_, bp, pd, pre, na_, bd_, dR_.as<c128>(), refine, ir_.conv, st));
+  IrState irb = ir_;  // the border's solution is no part of the column maxima
+  irb.ynorm = dynormb_.as<unsigned long long>();
+  NEP_HIP(solve_run<float>(spb_, dpdb_.as<ProbDesc>(), dmdb_.as<MatDesc>(), na_, bd_.S, drowsb_.as<int>(),
+                           ddinvb_.as<c64>(), ddinvb_off_.as<long long>(), bd_.RS, bd_.YS, true, ir_.conv, irb, st));
+  NEP_HIP(bd_solve_post(bdt_, bp, pd, pre, bd_, dY_.as<c128>(), refine, ir_.conv, ir_, st));
+  return NEP_OK;
+}
+
 nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, hipStream_t st) {
   // Z blocks of the low-rank terms of real problems (the complex-term
   // residual multiplies every term densely)
@@ -233,6 +381,7 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
       const int rk = (i < q.op->ell && !q.op->a_cplx) ? q.op->lr_rank[i] : 0;
       D.a_lr[i] = rk;
       D.LrG[i] = rk > 0 ? q.op->dLrG[i] : nullptr;
+      D.LrH[i] = rk > 0 ? q.op->dLrH[i] : nullptr;
       D.LrZ[i] = rk > 0 ? dlrz_.as<c128>() + zoff : nullptr;
       if (rk > 0) {
         int S, srows;
@@ -334,6 +483,12 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     D.band = o.dense ? 0 : band_of(*probs[p].op);
     D.offF = offF;
     D.offP = offP;
+    {
+      // the refinement, and the dense FP64 re-solve behind it, have to be there
+      int rank, nch;
+      D.bordered = !D.band && !o.dense && o.prec == NEP_PREC_C32_IR64 && o.max_refine > 0 && o.fallback &&
+                   bordered_of(*probs[p].op, rank, nch) >= 0;
+    }
     for (int j = 0; j < o.N; ++j, ++g) {
       MatDesc m;
       m.n = n;
@@ -342,14 +497,14 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
       m.offRow = offRow + j * n;
       m.node = g;
       all.push_back(m);
-      if (!D.band) dense.push_back(m);
+      if (!D.band && !D.bordered) dense.push_back(m);
       hprob.push_back(p);
       hj.push_back(j);
     }
     if (D.band) {
       offF += (long long)o.N * n * band_entries(D.band);
       offP += (long long)o.N * n;
-    } else {
+    } else if (!D.bordered) {
       offT += (long long)o.N * D.strideT;
     }
     offW += (long long)o.N * n * o.L;
@@ -358,6 +513,19 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   }
   nnodes = g;
   t_elems_ = offT;
+  sorted64_ = dense;
+  for (int p = 0; p < nprob; ++p) {  // after the dense blocks, in the FP64 re-solve's buffer only
+    ProbDesc& D = hpd_[p];
+    if (!D.bordered) continue;
+    D.offT0 = offT;
+    for (int j = 0; j < o.N; ++j) {
+      MatDesc m = all[(size_t)D.node0 + j];
+      m.offT = offT + (long long)j * D.strideT;
+      sorted64_.push_back(m);
+    }
+    offT += (long long)o.N * D.strideT;
+  }
+  t64_elems_ = offT;
   w_elems_ = offW;
   y_elems_ = offY;
   rows_total_ = offRow;
@@ -368,14 +536,16 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   std::stable_sort(sorted_.begin(), sorted_.end(), larger);
   shapes_ = all;
   std::stable_sort(shapes_.begin(), shapes_.end(), larger);
+  std::stable_sort(sorted64_.begin(), sorted64_.end(), larger);
 
   lu_.build(sorted_, o.prec);
   const bool mixed = o.prec == NEP_PREC_C32_IR64;
 
   hprefix_.clear();
   SolvePlan_build(sp_, hprefix_, sorted_, o.L, o.prec, dinv_off_, dinv_elems_);
+  SolvePlan_build(sp64_, hprefix_, sorted64_, o.L, o.prec, dinv64_off_, dinv64_elems_);
   {
-    std::vector<int> ca, cr, crr, cm;
+    std::vector<int> ca, ca64, cr, crr, cm;
     // real-term residual tiles: the big ones when they still give every CU
     // two groups (they halve the operand traffic per product)
     long long big_tiles = 0;
@@ -387,12 +557,14 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     for (int p = 0; p < nprob; ++p) {
       const long long n = hpd_[p].n;
       const bool cplx = probs[p].op->a_cplx != 0, band = hpd_[p].band != 0;
-      ca.push_back(band ? 0 : (int)ceil_div_ll(n * n, 256));
+      ca64.push_back(band ? 0 : (int)ceil_div_ll(n * n, 256));
+      ca.push_back(hpd_[p].bordered ? 0 : ca64.back());
       cr.push_back(band ? 0 : cplx ? ceil_div((int)n, 64) * ceil_div(2 * o.N * o.L, 64) : 0);
       crr.push_back(band || cplx ? 0 : ceil_div((int)n, rtm) * ceil_div(2 * o.N * o.L, rtq));
       cm.push_back(ceil_div((int)n * o.L, 256) * ceil_div(2 * o.K, 8));  // (row, column) blocks x moment groups
     }
     build_prefix(hprefix_, pt_.assemble, ca);
+    build_prefix(hprefix_, pt_.assemble64, ca64);
     build_prefix(hprefix_, pt_.resid, cr);
     build_prefix(hprefix_, pt_.resid_real, crr);
     build_prefix(hprefix_, pt_.moments, cm);
@@ -401,6 +573,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
 
   const size_t es = elem_size(o.prec);
   total_bytes_ = 0;
+  NEP_TRY(build_bordered(probs));
   auto A = [&](DevMem& m, size_t b) -> nep_status {
     nep_status s = m.alloc(b);
     total_bytes_ += b;
@@ -413,7 +586,9 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_TRY(A(dT_, es * (size_t)t_elems_));
   NEP_TRY(A(dF_, es * (size_t)f_elems_));
   NEP_TRY(A(dpiv_, (size_t)offP));
-  NEP_TRY(A(dpmin_, any_band_ ? sizeof(double) * (size_t)nnodes : 0));
+  NEP_TRY(A(dpmin_, any_band_ || !bp_.empty() ? sizeof(double) * (size_t)nnodes : 0));
+  NEP_TRY(A(dmd64_, bp_.empty() ? 0 : sizeof(MatDesc) * sorted64_.size()));
+  NEP_TRY(A(ddinv64_off_, bp_.empty() ? 0 : sizeof(long long) * sorted64_.size()));
   if (sp_.nblk > 0) {  // right-hand sides of the blocked solve
     NEP_TRY(A(dW_, sizeof(c64) * (size_t)sp_.nblk * sp_.npad * sp_.L));
     sp_.W = dW_.as<c64>();
@@ -428,6 +603,12 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     NEP_HIP(hipStreamCreateWithFlags(&ls_.side, hipStreamNonBlocking));
     for (hipEvent_t* e : {&ls_.ev_fork, &ls_.ev_join, &ls_.ev_side[0], &ls_.ev_side[1], &ls_.ev_side_done})
       NEP_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+  }
+  // a plan with both kinds of problems runs the band and bordered ones beside
+  // the dense ones: their chains leave most of the device idle
+  if (!sorted_.empty() && (any_band_ || !bp_.empty())) {
+    NEP_HIP(hipStreamCreateWithFlags(&beside_, hipStreamNonBlocking));
+    for (hipEvent_t& e : ev_beside_) NEP_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
   NEP_TRY(A(dinfo_, sizeof(int) * (size_t)nnodes));
   NEP_TRY(A(ddinv_, es * (size_t)dinv_elems_));
@@ -484,6 +665,12 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   }
 
   // pageable sources: each copy has taken its bytes when the call returns
+  NEP_TRY(upload_bordered(st));
+  if (!bp_.empty()) {
+    NEP_HIP(hipMemcpyAsync(dmd64_.p, sorted64_.data(), sizeof(MatDesc) * sorted64_.size(), hipMemcpyHostToDevice, st));
+    NEP_HIP(hipMemcpyAsync(ddinv64_off_.p, dinv64_off_.data(), sizeof(long long) * dinv64_off_.size(),
+                           hipMemcpyHostToDevice, st));
+  }
   if (!sorted_.empty()) {
     NEP_HIP(hipMemcpyAsync(dmd_.p, sorted_.data(), sizeof(MatDesc) * sorted_.size(), hipMemcpyHostToDevice, st));
     NEP_HIP(hipMemcpyAsync(ddinv_off_.p, dinv_off_.data(), sizeof(long long) * dinv_off_.size(),
@@ -498,6 +685,16 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_HIP(hipMemcpyAsync(na_.jnode, hj.data(), sizeof(int) * G, hipMemcpyHostToDevice, st));
   release_fallback();
   return upload_problems(probs, st);
+}
+
+// Factors of the band and bordered problems.
+template <typename P>
+nep_status MomentsPlan::structured_factor(hipStream_t st) {
+  if (any_band_)
+    NEP_HIP(band_factor<P>(bt_, dpd_.as<ProbDesc>(), dprefix_.as<int>(), na_, dF_.as<cx<P>>(),
+                           dpiv_.as<unsigned char>(), dinfo_.as<int>(), dpmin_.as<double>(), nullptr, st));
+  if (!bp_.empty()) NEP_TRY(bordered_factor(st));
+  return NEP_OK;
 }
 
 template <typename P>
@@ -519,20 +716,51 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   NEP_HIP(launch_vnorm(pd, nprob, opt.L, ir_, st));
   cx<P>* Dinv = ddinv_.as<cx<P>>();
   const long long* doff = ddinv_off_.as<long long>();
+  hipStream_t beside = beside_;
+  if (beside != nullptr && !bp_.empty()) {
+    // a captured pass keeps the bordered problems on st: a captured fork of
+    // their chain beside the dense LU's own forks ended in a fault of the
+    // runtime when the graph was made
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    NEP_HIP(hipStreamIsCapturing(st, &cs));
+    if (cs != hipStreamCaptureStatusNone) beside = nullptr;
+  }
   if (refactor) {  // otherwise the factors (and info) of the previous pass are reused
     if (eager) NEP_HIP(hipEventRecord(ev_lu_[0], st));
+    if (beside != nullptr) {
+      NEP_HIP(hipEventRecord(ev_beside_[0], st));
+      NEP_HIP(hipStreamWaitEvent(beside, ev_beside_[0], 0));
+      NEP_TRY(structured_factor<P>(beside));
+      NEP_HIP(hipEventRecord(ev_beside_[1], beside));
+    }
     NEP_HIP(lu_run<P>(lu_, md, dlu_prefix_.as<int>(), T, rows, drows_snap_.as<int>(), rows_total_, info, nullptr,
                       dlinv_.as<cx<P>>(), Dinv, doff, darrive_.as<int>(), st, ls_));
-    if (any_band_)
-      NEP_HIP(band_factor<P>(bt_, pd, pre, na_, dF_.as<cx<P>>(), piv, info, dpmin_.as<double>(), nullptr, st));
+    if (beside != nullptr) NEP_HIP(hipStreamWaitEvent(st, ev_beside_[1], 0));
+    else NEP_TRY(structured_factor<P>(st));
     if (eager) {
       NEP_HIP(hipEventRecord(ev_lu_[1], st));
       lu_timed_ = true;
     }
   }
   // nodes of problems sitting out the pass are marked converged by k_coef
-  NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, nullptr, Y, false, ir_.conv, ir_, st));
-  if (any_band_) NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, kBandV, ir_.conv, ir_, st));
+  auto solve = [&](bool refine) -> nep_status {
+    hipStream_t sx = beside != nullptr ? beside : st;
+    if (sx != st) {
+      NEP_HIP(hipEventRecord(ev_beside_[0], st));
+      NEP_HIP(hipStreamWaitEvent(sx, ev_beside_[0], 0));
+    }
+    if (any_band_)
+      NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, refine ? kBandRefine : kBandV, ir_.conv, ir_,
+                            sx));
+    if (!bp_.empty()) NEP_TRY(bordered_solve(refine, sx));
+    NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, refine ? R : nullptr, Y, refine, ir_.conv, ir_, st));
+    if (sx != st) {
+      NEP_HIP(hipEventRecord(ev_beside_[1], sx));
+      NEP_HIP(hipStreamWaitEvent(st, ev_beside_[1], 0));
+    }
+    return NEP_OK;
+  };
+  NEP_TRY(solve(false));
   sweeps_run_ = 0;
   if (opt.max_refine > 0) {
     // The correction solve of each sweep is queued before the host reads the
@@ -549,10 +777,7 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
         NEP_HIP(hipMemcpyAsync(hcounter_, ir_.counters, sizeof(int), hipMemcpyDeviceToHost, st));
         NEP_HIP(hipEventRecord(ev_counter_, st));
       }
-      if (s < opt.max_refine) {
-        NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, R, Y, true, ir_.conv, ir_, st));
-        if (any_band_) NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, kBandRefine, ir_.conv, ir_, st));
-      }
+      if (s < opt.max_refine) NEP_TRY(solve(true));
       if (eager) {
         NEP_HIP(hipEventSynchronize(ev_counter_));
         if (hcounter_[0] == 0) break;
@@ -574,9 +799,9 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   static_assert(sizeof(P) == 8, "fallback runs in FP64");
   if (!dT64_.p && !dF64_.p) {
     auto alloc64 = [&]() -> nep_status {
-      nep_status s = dT64_.alloc(sizeof(c128) * (size_t)t_elems_);
-      if (s == NEP_OK) s = ddinv64_.alloc(sizeof(c128) * (size_t)dinv_elems_);
-      if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted_.size() * kLuMaxJB * kLuMaxJB);
+      nep_status s = dT64_.alloc(sizeof(c128) * (size_t)t64_elems_);
+      if (s == NEP_OK) s = ddinv64_.alloc(sizeof(c128) * (size_t)dinv64_elems_);
+      if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted64_.size() * kLuMaxJB * kLuMaxJB);
       if (s == NEP_OK) s = dF64_.alloc(sizeof(c128) * (size_t)f_elems_);
       if (s == NEP_OK) s = dpiv64_.alloc(dpiv_.bytes);
       if (s == NEP_OK) s = dpmin64_.alloc(dpmin_.bytes);
@@ -598,7 +823,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_TRY(s);
   }
   const ProbDesc* pd = dpd_.as<ProbDesc>();
-  const MatDesc* md = dmd_.as<MatDesc>();
+  const MatDesc* md = bp_.empty() ? dmd_.as<MatDesc>() : dmd64_.as<MatDesc>();
   const int* pre = dprefix_.as<int>();
   c128* T = dT64_.as<c128>();
   const int* skip = ir_.conv;
@@ -610,9 +835,9 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     for (int p = 0; p < nprob; ++p)
       for (int j = 0; j < opt.N; ++j) fallback_count_[p] += conv[hpd_[p].node0 + j] ? 0 : 1;
   }
-  NEP_HIP(launch_assemble<double>(pd, pre, pt_.assemble, na_, T, skip, st));
+  NEP_HIP(launch_assemble<double>(pd, pre, pt_.assemble64, na_, T, skip, st));
   c128* Dinv = ddinv64_.as<c128>();
-  const long long* doff = ddinv_off_.as<long long>();
+  const long long* doff = bp_.empty() ? ddinv_off_.as<long long>() : ddinv64_off_.as<long long>();
   {
     // factor only the unconverged matrices: a compact plan over them (in the
     // size order of the full plan), whose diagonal-block inverses land where
@@ -622,10 +847,10 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_HIP(hipStreamSynchronize(st));
     std::vector<MatDesc> sub;
     std::vector<long long> sub_off;
-    for (size_t b = 0; b < sorted_.size(); ++b)
-      if (!conv[sorted_[b].node]) {
-        sub.push_back(sorted_[b]);
-        sub_off.push_back(dinv_off_[b]);
+    for (size_t b = 0; b < sorted64_.size(); ++b)
+      if (!conv[sorted64_[b].node]) {
+        sub.push_back(sorted64_[b]);
+        sub_off.push_back(dinv64_off_[b]);
       }
     if (!sub.empty()) {
       LuPlan lsub;
@@ -651,7 +876,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   if (any_band_)
     NEP_HIP(band_factor<double>(bt_, pd, pre, na_, dF64_.as<c128>(), piv, dinfo_.as<int>(), dpmin64_.as<double>(),
                                 skip, st));
-  NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
+  NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
                             skip, ir_, st));
   if (any_band_)
     NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandV, skip, ir_,
@@ -665,7 +890,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_HIP(hipMemcpyAsync(hcounter_, ir_.counters, sizeof(int), hipMemcpyDeviceToHost, st));
     NEP_HIP(hipStreamSynchronize(st));
     if (hcounter_[0] == 0) break;
-    NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
+    NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
                               true, ir_.conv, ir_, st));
     if (any_band_)
       NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandRefine, ir_.conv,
@@ -684,10 +909,7 @@ nep_status MomentsPlan::factor_t(hipStream_t st) {
   NEP_HIP(lu_run<P>(lu_, dmd_.as<MatDesc>(), dlu_prefix_.as<int>(), dT_.as<cx<P>>(), drows_.as<int>(),
                     drows_snap_.as<int>(), rows_total_, dinfo_.as<int>(), nullptr, dlinv_.as<cx<P>>(),
                     ddinv_.as<cx<P>>(), ddinv_off_.as<long long>(), darrive_.as<int>(), st, ls_));
-  if (any_band_)
-    NEP_HIP(band_factor<P>(bt_, pd, dprefix_.as<int>(), na_, dF_.as<cx<P>>(), dpiv_.as<unsigned char>(),
-                           dinfo_.as<int>(), dpmin_.as<double>(), nullptr, st));
-  return NEP_OK;
+  return structured_factor<P>(st);
 }
 
 template <typename P>
@@ -739,6 +961,9 @@ nep_status MomentsPlan::logdet(hipStream_t st, std::vector<double>& logabs, std:
     else
       NEP_HIP(band_logdet<float>(bt_, pd, dprefix_.as<int>(), dF_.as<c64>(), piv, nnodes, out.as<double>(), st));
   }
+  if (!bp_.empty())
+    NEP_HIP(bd_pivots(bdt_, dbp_.as<BdProb>(), dpd_.as<ProbDesc>(), dprefix_.as<int>(), bd_, drowsb_.as<int>(),
+                      dpmin_.as<double>(), out.as<double>(), nnodes, st));
   std::vector<double> h(2 * (size_t)nnodes);
   NEP_HIP(hipMemcpyAsync(h.data(), out.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
   NEP_HIP(hipStreamSynchronize(st));

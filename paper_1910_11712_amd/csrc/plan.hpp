@@ -130,6 +130,9 @@ class MomentsPlan {
       if (e) (void)hipEventDestroy(e);
     if (ls_.aux) (void)hipStreamDestroy(ls_.aux);
     if (ls_.side) (void)hipStreamDestroy(ls_.side);
+    for (hipEvent_t e : ev_beside_)
+      if (e) (void)hipEventDestroy(e);
+    if (beside_) (void)hipStreamDestroy(beside_);
   }
   // Builds layout, tables and buffers.  Problems may differ in n (ragged).
   // The device tables are uploaded on st, the stream the plan's passes run
@@ -222,6 +225,8 @@ class MomentsPlan {
   template <typename P>
   nep_status enqueue_t(hipStream_t st, bool eager, bool refactor);
   template <typename P>
+  nep_status structured_factor(hipStream_t st);
+  template <typename P>
   nep_status run_fallback(hipStream_t st);
   template <typename P>
   nep_status factor_t(hipStream_t st);
@@ -242,6 +247,31 @@ class MomentsPlan {
   bool any_band_ = false;
   DevMem dF_, dF64_, dpiv_, dpiv64_, dpmin_, dpmin64_;   // their factors, pivots and smallest pivot moduli
   long long f_elems_ = 0;
+  // bordered problems (border.hip): their factors, and their border systems'
+  // LU and solve (node g of the plan is node g there)
+  nep_status build_bordered(const std::vector<PlanProblem>& probs);
+  nep_status upload_bordered(hipStream_t st);
+  nep_status bordered_factor(hipStream_t st);
+  nep_status bordered_solve(bool refine, hipStream_t st);
+  std::vector<BdProb> bp_;
+  BdTables bdt_;
+  BdBufs bd_{};
+  LuPlan lub_;
+  SolvePlan spb_;
+  std::vector<MatDesc> sortedb_;
+  std::vector<ProbDesc> hpdb_;          // the border systems' right-hand side layout
+  std::vector<long long> dinvb_off_;
+  long long dinvb_elems_ = 0;
+  int rowsb_total_ = 0;
+  DevMem dbp_, dbd_[10], dmdb_, dpdb_, dlub_prefix_, drowsb_, drowsb_snap_, dinfob_, ddinvb_, ddinvb_off_, dlinvb_,
+      darriveb_, dynormb_;
+  // an FP64 re-solve factors the bordered problems' nodes densely as well:
+  // the matrices, solve plan and tables of dense and bordered problems
+  std::vector<MatDesc> sorted64_;
+  SolvePlan sp64_;
+  std::vector<long long> dinv64_off_;
+  long long dinv64_elems_ = 0, t64_elems_ = 0;
+  DevMem dmd64_, ddinv64_off_;
   std::vector<int> hprefix_;
   DevMem dpd_, dmd_, dprefix_, dlu_prefix_;
   DevMem dT_, drows_, drows_snap_, dinfo_, dY_, dR_, dnode_, dir_, dT64_, dW_;
@@ -257,6 +287,8 @@ class MomentsPlan {
   DevMem dstat_;                     // status block gathered for finish()
   char* hstat_ = nullptr;            // its pinned host copy
   size_t hstat_bytes_ = 0;
+  hipStream_t beside_ = nullptr;  // band and bordered problems of a plan that has dense ones too
+  hipEvent_t ev_beside_[2] = {nullptr, nullptr};
   LuStreams ls_;  // look-ahead LU streams (default priority) and events
   size_t total_bytes_ = 0;
   long long t_elems_ = 0, w_elems_ = 0, y_elems_ = 0;
