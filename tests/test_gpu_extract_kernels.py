@@ -1,0 +1,59 @@
+"""The extraction's QR panels, device SVD and compact-WY product at the edges of
+their row and column ranges (panels of 8 and 4 columns with one to four rows a thread and the path beyond
+them, 63 to 80 columns around the device SVD's limit): moments of a known operator go in, eigenvalues, eigenvectors and
+singular values are compared with the FP64 oracle's extraction of the same
+moments."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from workloads import Contour, Problem
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def nep():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    import paper_1910_11712_amd as P
+    P.binding.lib()
+    return P
+
+
+# (n, L, K): K n rows and K L columns of the block Hankel matrix
+@pytest.mark.parametrize("n,L,K", [(40, 5, 1), (40, 4, 4), (127, 3, 4), (128, 4, 4), (129, 17, 1), (257, 2, 2),
+                                   (512, 7, 2), (513, 9, 2), (1024, 16, 1), (1025, 9, 2), (700, 21, 3), (700, 16, 4),
+                                   (700, 13, 5), (2050, 8, 2), (2100, 20, 4)])
+def test_extraction_matches_oracle(nep, n, L, K):
+    """A diagonal operator with a few eigenvalues inside: the moments are
+    exact, S_p = sum over the eigenvalues, so the oracle's extraction is cheap
+    at every size."""
+    rng = np.random.default_rng([n, L, K])
+    inside = min(3, K * L - 1)
+    d = np.concatenate([[0.3 + 0.1j, -0.4j, -0.5 + 0.2j][:inside], 3.0 + rng.uniform(0.0, 4.0, n - inside)])
+    con, N = Contour.circle(0.0, 1.0), 64
+    p = Problem("diag", [np.diag(d), np.eye(n)], [wl.fn_rational([1.0]), wl.fn_rational([-1.0, 0.0])])
+    V = wl.probes(n, L, 3)
+    # exact discrete filter: sum_j w_j zeta_j^q / (d - z_j) for every diagonal entry
+    z = np.exp(2j * np.pi * (np.arange(N) + 0.5) / N)
+    S = np.stack([(np.sum((z / N) * z ** q / (d[:, None] - z), axis=1))[:, None] * V for q in range(2 * K)])
+    op = nep.SplitOperator.from_problem(p)
+    Sd = torch.from_numpy(np.ascontiguousarray(S.transpose(0, 2, 1))).to("cuda")
+    r = op.extract(con, Sd, N, L, K, max_eigs=K * L, rank_tol=1e-10)
+    ro = oracle.extract(p, con, S, K, rank_tol=1e-10)
+    assert r["m"] == len(ro["lam"]), (r["m"], len(ro["lam"]))
+    sv = np.linalg.svd(np.block([[S[a + b] for b in range(K)] for a in range(K)]), compute_uv=False)
+    assert np.max(np.abs(r["sigma"] - sv)) <= 1e-13 * sv[0]
+    got, ref = r["lam"][r["inside"]], d[:inside]
+    assert len(got) == inside, r["lam"]
+    for k in range(inside):
+        q = int(np.argmin(np.abs(r["lam"] - ref[k])))
+        assert abs(r["lam"][q] - ref[k]) <= 1e-12
+        x = r["X"][:, q]
+        assert abs(np.linalg.norm(x) - 1.0) <= 1e-13 and abs(x[k] - 1.0) <= 1e-11, (k, x[k])
+        assert r["eta"][q] <= 1e-12
+    op.close()
