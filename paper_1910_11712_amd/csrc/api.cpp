@@ -136,20 +136,27 @@ static int detect_low_rank(int n, const double* h, long long ld, int rmax, std::
   // The first r columns of Y alone are a random r x r mixture of A's range,
   // now and then ill-conditioned enough to spoil Q_r beyond the check below;
   // the r columns that pivoting picks out of r + 8 or more are not.
-  std::vector<double> tau(k, 0.0), diag(k, 0.0);
+  // (the columns' remaining norms are updated, and formed again where the
+  // update has cancelled)
+  std::vector<double> tau(k, 0.0), diag(k, 0.0), left(k), full(k);
+  auto norm2_from = [&](int jj, int j) {
+    const double* y = &Y[(size_t)jj * n];
+    double s = 0.0;
+    for (int r = j; r < n; ++r) s += y[r] * y[r];
+    return s;
+  };
+  for (int j = 0; j < k; ++j) left[j] = full[j] = norm2_from(j, 0);
   for (int j = 0; j < k; ++j) {
     int best = j;
-    double top = -1.0;
     for (int jj = j; jj < k; ++jj) {
-      const double* y = &Y[(size_t)jj * n];
-      double s = 0.0;
-      for (int r = j; r < n; ++r) s += y[r] * y[r];
-      if (s > top) {
-        top = s;
-        best = jj;
-      }
+      if (left[jj] < 1e-6 * full[jj]) left[jj] = full[jj] = norm2_from(jj, j);
+      if (left[jj] > left[best]) best = jj;
     }
-    if (best != j) std::swap_ranges(&Y[(size_t)j * n], &Y[(size_t)j * n] + n, &Y[(size_t)best * n]);
+    if (best != j) {
+      std::swap_ranges(&Y[(size_t)j * n], &Y[(size_t)j * n] + n, &Y[(size_t)best * n]);
+      std::swap(left[j], left[best]);
+      std::swap(full[j], full[best]);
+    }
     double* x = &Y[(size_t)j * n];
     double s2 = 0.0;
     for (int r = j + 1; r < n; ++r) s2 += x[r] * x[r];
@@ -169,6 +176,7 @@ static int detect_low_rank(int n, const double* h, long long ld, int rmax, std::
       w *= tau[j];
       b[j] -= w;
       for (int r = j + 1; r < n; ++r) b[r] -= x[r] * w;
+      left[jj] -= b[j] * b[j];
     }
   }
   int rk = 0;
@@ -259,6 +267,7 @@ nep_status Split::init(int n_, int ell_, const nep_mat* A, const nep_fn* f, hipS
   op.dfn_coef = fn_coef.as<c128>();
   h_fn_nodes = nodes;
   h_fn_coef = coef;
+  std::vector<std::vector<double>> allG, allH;  // the low-rank terms' factors, in term order
   // matrices: upload column-major, convert to row-major on the device
   NEP_TRY(norms.alloc(sizeof(double) * kMaxTerms + sizeof(unsigned long long) * 2));
   op.dnormA = norms.as<double>();
@@ -318,6 +327,8 @@ nep_status Split::init(int n_, int ell_, const nep_mat* A, const nep_fn* f, hipS
           std::vector<double> hG, hH;
           const int rk = detect_low_rank(n_, h, A[i].ld, std::min(kLowRankMax, n_ / 8), hG, hH);
           if (rk > 0) {
+            allG.push_back(hG);
+            allH.push_back(hH);
             lrG[i] = std::make_unique<DevMem>();
             lrH[i] = std::make_unique<DevMem>();
             NEP_TRY(lrG[i]->alloc(sizeof(double) * hG.size()));
@@ -334,6 +345,29 @@ nep_status Split::init(int n_, int ell_, const nep_mat* A, const nep_fn* f, hipS
     NEP_HIP(inf_norm(mats[i]->p, n_, cplx, scratch, norms.as<double>() + i, stream));
     NEP_HIP(hipStreamSynchronize(stream));  // staging is released at scope end
     op.dA[i] = mats[i]->p;
+  }
+  if (!allG.empty()) {  // side by side in FP32, rows and columns padded to whole blocks, for the bordered factors
+    int rank = 0;
+    for (const auto& G : allG) rank += (int)(G.size() / n_);
+    const size_t rp = (size_t)ceil_div(rank, kBdBlk) * kBdBlk, rows = (size_t)ceil_div(n_, kBdBlk) * kBdBlk;
+    std::vector<float> g(rows * rp, 0.f), hh(rows * rp, 0.f);
+    size_t c0 = 0;
+    for (size_t t = 0; t < allG.size(); ++t) {
+      const size_t rk = allG[t].size() / n_;
+      for (int r = 0; r < n_; ++r)
+        for (size_t j = 0; j < rk; ++j) {
+          g[r * rp + c0 + j] = (float)allG[t][r * rk + j];
+          hh[r * rp + c0 + j] = (float)allH[t][r * rk + j];
+        }
+      c0 += rk;
+    }
+    NEP_TRY(lr32.alloc(2 * sizeof(float) * g.size()));
+    NEP_HIP(hipMemcpyAsync(lr32.p, g.data(), sizeof(float) * g.size(), hipMemcpyHostToDevice, stream));
+    NEP_HIP(hipMemcpyAsync(lr32.as<float>() + g.size(), hh.data(), sizeof(float) * g.size(), hipMemcpyHostToDevice,
+                           stream));
+    NEP_HIP(hipStreamSynchronize(stream));
+    op.dG32 = lr32.as<float>();
+    op.dH32 = lr32.as<float>() + g.size();
   }
   op.normA.assign(ell_, 0.0);
   NEP_HIP(hipMemcpyAsync(op.normA.data(), op.dnormA, sizeof(double) * ell_, hipMemcpyDeviceToHost, stream));

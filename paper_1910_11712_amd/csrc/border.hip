@@ -59,31 +59,50 @@ __device__ __forceinline__ c64 bd_elem(const ProbDesc& D, const c128* __restrict
   return c64{float(sr), float(si)};
 }
 
-// f_i G_i[gr][.] for column h of the concatenated low-rank terms (zero past the ranks and past n)
-__device__ __forceinline__ c64 bd_lowrank(const ProbDesc& D, const c128* __restrict__ f, int gr, int h) {
-  if (gr >= D.n) return c64{0.f, 0.f};
+// the f_i of column h of the concatenated low-rank terms
+__device__ __forceinline__ c128 bd_lowrank_f(const ProbDesc& D, const c128* __restrict__ f, int h) {
   for (int i = 0; i < D.ell; ++i) {
-    const int r = D.a_lr[i];
-    if (r == 0) continue;
-    if (h < r) {
-      const double g = D.LrG[i][(long long)gr * r + h];
-      return c64{float(f[i].re * g), float(f[i].im * g)};
-    }
-    h -= r;
+    if (D.a_lr[i] == 0) continue;
+    if (h < D.a_lr[i]) return f[i];
+    h -= D.a_lr[i];
   }
-  return c64{0.f, 0.f};
+  return c128{0.0, 0.0};
 }
+// f times an entry of its G
+__device__ __forceinline__ c64 bd_lowrank(c128 f, float g) { return c64{float(f.re * g), float(f.im * g)}; }
 
-__device__ __forceinline__ float bd_h(const ProbDesc& D, int gr, int h) {
-  if (gr >= D.n) return 0.f;
-  for (int i = 0; i < D.ell; ++i) {
-    const int r = D.a_lr[i];
-    if (r == 0) continue;
-    if (h < r) return float(D.LrH[i][(long long)gr * r + h]);
-    h -= r;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// An 8 x 16 complex tile on v_mfma_f32_16x16x4f32 and the real 2x2 embedding:
+// lane l feeds A row l%16 (complex row l%16/2, component l%2) and k-slot l/16
+// (half l/32 of the complex k, component l/16%2), B column l%16; accumulator
+// register r is complex row 2 (l/16) + r/2, component r%2, column l%16.
+struct BdTile {
+  int arow, acomp, crow, col, ku, kh;
+  float asign;
+  __device__ __forceinline__ BdTile(int rb, int cb) {
+    const int l = threadIdx.x & 63, at = l & 1;
+    ku = (l >> 4) & 1;
+    kh = l >> 5;
+    arow = rb + ((l & 15) >> 1);
+    acomp = at ^ ku;
+    crow = rb + 2 * (l >> 4);
+    col = cb + (l & 15);
+    asign = (at == 0 && ku == 1) ? -1.f : 1.f;
   }
-  return 0.f;
-}
+  // acc += sign A B over K complex k: A row-major in LDS, b(k) this lane's
+  // column of B's row k
+  template <int K, int LDA, typename F>
+  __device__ __forceinline__ floatx4 mul(const c64 (*A)[LDA], float sign, floatx4 acc, F&& b) const {
+    const float* a = reinterpret_cast<const float*>(&A[arow][kh * (K / 2)]) + acomp;
+    const float sg = sign * asign;
+#pragma unroll
+    for (int x = 0; x < K / 2; ++x)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sg * a[2 * x], ku ? b(kh * (K / 2) + x).im : b(kh * (K / 2) + x).re,
+                                                 acc, 0, 0, 0);
+    return acc;
+  }
+};
 
 // One complex k of a 16 x 32 complex product on the 2x2 real embedding: lane l
 // feeds A row (l%32)/2, component l%2, with the sign of the embedding, and B
@@ -129,19 +148,24 @@ __device__ __forceinline__ float bd_readlane(float v, int l) {
 }
 
 // ---------------------------------------------------------------------------
-// Chunk factorization: one group of four waves per (node, chunk), the 64 x 96
+// Chunk factorization: one group of eight waves per (node, chunk), the 64 x 96
 // window of the current block in LDS.  Per block: wave 0 factors the 64 x 32
 // panel with one row per lane in registers (pivot rows stay in their lanes and
 // are broadcast by readlane, no exchange), while the other waves assemble the
-// rows that enter next; then L11 and U11 are inverted (one column per lane, a
-// wave each), and all waves form U12 = L11^-1 A12 and A22 - L21 U12 on the
-// matrix cores.  Bound by the chain of panels; the chunks are what cuts it.
-// Per block the store holds L11^-1, L21, U11^-1 and U12's two 32 x 32 blocks.
+// rows that enter next; L11 and U11 are inverted (16 x 16 diagonal blocks, one
+// column per lane, four waves; then their off-diagonal blocks as products);
+// and all waves form U12 = L11^-1 A12 and A22 - L21 U12 on the matrix cores.
+// Bound by the chain of panels (12 of 20 us per block); the chunks are what
+// cuts it.  64 nodes of n = 4096: 0.63 ms (four waves, with 32-step inverses:
+// 1.03).  Per block the store holds L11^-1, L21, U11^-1 and U12's two 32 x 32
+// blocks.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bd_lu(const BdProb* __restrict__ bp, const int* __restrict__ prefix, int cnt,
-                                               const ProbDesc* __restrict__ pd, NodeArrays na,
-                                               c64* __restrict__ blocks, unsigned char* __restrict__ perms,
-                                               c64* __restrict__ pivots, int* __restrict__ info) {
+constexpr int kBdLuThreads = 512;
+
+__global__ __launch_bounds__(kBdLuThreads) void k_bd_lu(const BdProb* __restrict__ bp, const int* __restrict__ prefix,
+                                                        int cnt, const ProbDesc* __restrict__ pd, NodeArrays na,
+                                                        c64* __restrict__ blocks, unsigned char* __restrict__ perms,
+                                                        c64* __restrict__ pivots, int* __restrict__ info) {
   const int v = blockIdx.x;
   const int s = find_slot(prefix, cnt, v);
   const BdProb& q = bp[s];
@@ -153,11 +177,12 @@ __global__ __launch_bounds__(256) void k_bd_lu(const BdProb* __restrict__ bp, co
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (c == 0 && tid == 0) info[g] = D.n;  // a zero pivot here is left to the refinement
 
+  constexpr int H = B / 2;
   __shared__ c64 Wn[2 * B][3 * B + 1];  // window: rows of the current block, then of the next
   __shared__ c64 Nx[B][3 * B + 1];      // rows entering next
   __shared__ c64 LU[2 * B][B + 1];      // panel in pivot order
   __shared__ c64 Li[B][B + 1], Ui[B][B + 1];
-  __shared__ c64 U12[B][2 * B + 1];
+  __shared__ c64 U12[B][2 * B + 1];     // (its first rows hold the inverses' products before)
   __shared__ int src[2 * B];
 
   c64* __restrict__ bout = blocks + q.offB + ((long long)j * q.nb + st) * 5 * B2;
@@ -170,12 +195,13 @@ __global__ __launch_bounds__(256) void k_bd_lu(const BdProb* __restrict__ bp, co
     if (kb >= len || cb >= len) return c64{0.f, 0.f};
     return bd_elem(D, f, w, (st + kb) * B + i, (st + cb) * B + (col & (B - 1)));
   };
-  for (int e = tid; e < 2 * B * 3 * B; e += 256) {
+  for (int e = tid; e < 2 * B * 3 * B; e += kBdLuThreads) {
     const int i = e / (3 * B), col = e - i * 3 * B;
     Wn[i][col] = row_elem(i / B, i & (B - 1), 0, col);
   }
   __syncthreads();
-  const BdLane bl;
+  const BdTile t0((wave & 3) * 8, (wave >> 2) * B), t1((wave & 3) * 8, (wave >> 2) * B + 16);
+  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   for (int k = 0; k < len; ++k) {
     const bool more = k + 1 < len;
     if (wave == 0) {
@@ -219,74 +245,149 @@ __global__ __launch_bounds__(256) void k_bd_lu(const BdProb* __restrict__ bp, co
       pout[(long long)k * 2 * B + pos] = (unsigned char)lane;
       if (lane < B) vout[(long long)k * B + lane] = c64{dre, dim};
     } else if (more) {
-      for (int e = tid - 64; e < B * 3 * B; e += 192) {
-        const int i = e / (3 * B), col = e - i * 3 * B;
-        Nx[i][col] = row_elem(k + 2, i, k + 1, col);
+      // the entering rows (block k + 2, columns from block k + 1 on), term by
+      // term, every entry's load of a term in flight together
+      constexpr int ET = kBdLuThreads - 64, EU = (B * 3 * B + ET - 1) / ET;
+      double sr[EU], si[EU];
+      int off[EU];  // entry's offset in a dense term, -1: outside the band or the chunk
+#pragma unroll
+      for (int u = 0; u < EU; ++u) {
+        const int e = tid - 64 + ET * u, i = e / (3 * B), col = e - i * 3 * B;
+        const int kb = k + 2, cb = k + 1 + col / B;
+        const int gr = (st + kb) * B + i, gc = (st + cb) * B + (col & (B - 1)), d = gr - gc;
+        const bool blk = e < B * 3 * B && kb < len && cb < len, in = blk && gr < D.n && gc < D.n;
+        off[u] = in && d <= w && d >= -w ? gr * D.n + gc : -1;
+        sr[u] = blk && !in && d == 0 ? 1.0 : 0.0;  // identity past n
+        si[u] = 0.0;
+      }
+      for (int t = 0; t < D.ell; ++t) {
+        if (D.a_lr[t] > 0) continue;
+        const c128 ft = f[t];
+        if (D.a_is_diag[t]) {
+#pragma unroll
+          for (int u = 0; u < EU; ++u) {
+            const int e = tid - 64 + ET * u, i = e / (3 * B), col = e - i * 3 * B;
+            if (col == B + i && off[u] >= 0) {
+              const c128 a = D.Adiag[t][(st + k + 2) * B + i];
+              sr[u] += ft.re * a.re - ft.im * a.im;
+              si[u] += ft.re * a.im + ft.im * a.re;
+            }
+          }
+          continue;
+        }
+        const double* __restrict__ A = reinterpret_cast<const double*>(D.A[t]);
+        double av[EU];
+#pragma unroll
+        for (int u = 0; u < EU; ++u) av[u] = A[max(off[u], 0)];
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+          const double a = off[u] >= 0 ? av[u] : 0.0;
+          sr[u] += ft.re * a;
+          si[u] += ft.im * a;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < EU; ++u) {
+        const int e = tid - 64 + ET * u, i = e / (3 * B), col = e - i * 3 * B;
+        if (e < B * 3 * B) Nx[i][col] = c64{float(sr[u]), float(si[u])};
       }
     }
     __syncthreads();
-    if (wave == 0 && lane < B) {  // column `lane` of L11^-1
-      c64 x[B];
+    // 16 x 16 diagonal blocks: waves 0, 1 of L11^-1, 2, 3 of U11^-1, column
+    // `lane`; each entry found updates the ones after it (independent sums)
+    if (wave < 4 && lane < H) {
+      const int o = (wave & 1) * H;
+      c64 x[H];
 #pragma unroll
-      for (int i = 0; i < B; ++i) {
-        c64 t = {i == lane ? 1.f : 0.f, 0.f};
+      for (int i = 0; i < H; ++i) x[i] = c64{i == lane ? 1.f : 0.f, 0.f};
+      if (wave < 2) {
 #pragma unroll
-        for (int m = 0; m < B; ++m)
-          if (m < i) t = fms(t, LU[i][m], x[m]);
-        x[i] = t;
-        Li[i][lane] = t;
+        for (int i = 0; i < H; ++i) {
+#pragma unroll
+          for (int m = i + 1; m < H; ++m) x[m] = fms(x[m], LU[o + m][o + i], x[i]);
+          Li[o + i][o + lane] = x[i];
+        }
+      } else {
+#pragma unroll
+        for (int i = H - 1; i >= 0; --i) {
+          x[i] = x[i] * recip_f32(LU[o + i][o + i]);
+#pragma unroll
+          for (int m = 0; m < i; ++m) x[m] = fms(x[m], LU[o + m][o + i], x[i]);
+          Ui[o + i][o + lane] = x[i];
+        }
       }
-    } else if (wave == 1 && lane < B) {  // column `lane` of U11^-1
-      c64 x[B];
-#pragma unroll
-      for (int i = B - 1; i >= 0; --i) {
-        c64 t = {i == lane ? 1.f : 0.f, 0.f};
-#pragma unroll
-        for (int m = B - 1; m > 0; --m)
-          if (m > i) t = fms(t, LU[i][m], x[m]);
-        x[i] = t * recip_f32(LU[i][i]);
-        Ui[i][lane] = x[i];
+    } else if (wave >= 4) {  // the blocks that stay zero
+      for (int e = tid - 256; e < H * H; e += 256) {
+        Li[e / H][H + e % H] = c64{0.f, 0.f};
+        Ui[H + e / H][e % H] = c64{0.f, 0.f};
+      }
+    }
+    __syncthreads();
+    // L: -C^-1 (B A^-1) below the diagonal; U: -A^-1 (B C^-1) above it
+    if (wave < 4) {
+      const bool up = wave >= 2;
+      const BdTile ti((wave & 1) * 8, 0);
+      floatx4 acc;
+      if (up)
+        acc = ti.mul<H>(reinterpret_cast<const c64(*)[B + 1]>(&LU[0][H]), 1.f, zero,
+                        [&](int x) { return Ui[H + x][H + ti.col]; });
+      else
+        acc = ti.mul<H>(reinterpret_cast<const c64(*)[B + 1]>(&LU[H][0]), 1.f, zero, [&](int x) { return Li[x][ti.col]; });
+      U12[ti.crow][(up ? H : 0) + ti.col] = c64{acc[0], acc[1]};
+      U12[ti.crow + 1][(up ? H : 0) + ti.col] = c64{acc[2], acc[3]};
+    }
+    __syncthreads();
+    if (wave < 4) {
+      const bool up = wave >= 2;
+      const BdTile ti((wave & 1) * 8, 0);
+      floatx4 acc;
+      if (up) {
+        acc = ti.mul<H>(reinterpret_cast<const c64(*)[B + 1]>(&Ui[0][0]), -1.f, zero,
+                        [&](int x) { return U12[x][H + ti.col]; });
+        Ui[ti.crow][H + ti.col] = c64{acc[0], acc[1]};
+        Ui[ti.crow + 1][H + ti.col] = c64{acc[2], acc[3]};
+      } else {
+        acc = ti.mul<H>(reinterpret_cast<const c64(*)[B + 1]>(&Li[H][H]), -1.f, zero,
+                        [&](int x) { return U12[x][ti.col]; });
+        Li[H + ti.crow][ti.col] = c64{acc[0], acc[1]};
+        Li[H + ti.crow + 1][ti.col] = c64{acc[2], acc[3]};
       }
     }
     __syncthreads();
     c64* __restrict__ bk = bout + (long long)k * 5 * B2;
-    for (int e = tid; e < B2; e += 256) {
+    for (int e = tid; e < B2; e += kBdLuThreads) {
       const int i = e / B, m = e & (B - 1);
       bk[e] = Li[i][m];
       bk[B2 + e] = LU[B + i][m];
       bk[2 * B2 + e] = Ui[i][m];
     }
     if (!more) break;
-    // U12 = L11^-1 A12 (the window's pivot rows, columns 32..95): a 16 x 32 tile per wave
-    const int rb = (wave & 1) * 16, cb = (wave >> 1) * B;
-    floatx16 acc = bd_zero();
-#pragma unroll 8
-    for (int m = 0; m < B; ++m)
-      acc = bd_mfma(bl.asign * bd_comp(Li[rb + bl.arow][m], bl.acomp), bd_comp(Wn[src[m]][B + cb + bl.bcol], bl.bcomp),
-                    acc);
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int i = rb + bl.crow(r);
-      const c64 u = {acc[r], acc[r + 1]};
-      U12[i][cb + bl.bcol] = u;
-      bk[(3 + (wave >> 1)) * B2 + i * B + bl.bcol] = u;
-    }
-    // A22 - L21 U12: the rows left over
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const c64 x = Wn[src[B + rb + bl.crow(r)]][B + cb + bl.bcol];
-      acc[r] = x.re;
-      acc[r + 1] = x.im;
-    }
+    // U12 = L11^-1 A12 (the window's pivot rows, columns 32..95): two 8 x 16 tiles per wave
+    floatx4 u0 = t0.mul<B>(Li, 1.f, zero, [&](int x) { return Wn[src[x]][B + t0.col]; });
+    floatx4 u1 = t1.mul<B>(Li, 1.f, zero, [&](int x) { return Wn[src[x]][B + t1.col]; });
+    // the rows left over, before any wave writes the window
+    const c64 x00 = Wn[src[B + t0.crow]][B + t0.col], x01 = Wn[src[B + t0.crow + 1]][B + t0.col];
+    const c64 x10 = Wn[src[B + t1.crow]][B + t1.col], x11 = Wn[src[B + t1.crow + 1]][B + t1.col];
+    auto put = [&](const BdTile& t, floatx4 u) {
+      U12[t.crow][t.col] = c64{u[0], u[1]};
+      U12[t.crow + 1][t.col] = c64{u[2], u[3]};
+      c64* bu = bk + (3 + (wave >> 2)) * B2 + t.crow * B + (t.col & (B - 1));
+      bu[0] = c64{u[0], u[1]};
+      bu[B] = c64{u[2], u[3]};
+    };
+    put(t0, u0);
+    put(t1, u1);
     __syncthreads();
-#pragma unroll 8
-    for (int m = 0; m < B; ++m)
-      acc = bd_mfma(-bl.asign * bd_comp(LU[B + rb + bl.arow][m], bl.acomp), bd_comp(U12[m][cb + bl.bcol], bl.bcomp),
-                    acc);
+    // A22 - L21 U12
+    const auto& L21 = *reinterpret_cast<const c64(*)[B][B + 1]>(&LU[B]);
+    u0 = t0.mul<B>(L21, -1.f, floatx4{x00.re, x00.im, x01.re, x01.im}, [&](int x) { return U12[x][t0.col]; });
+    u1 = t1.mul<B>(L21, -1.f, floatx4{x10.re, x10.im, x11.re, x11.im}, [&](int x) { return U12[x][t1.col]; });
     // the next window: the updated rows (columns shifted by a block), then the assembled ones
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) Wn[rb + bl.crow(r)][cb + bl.bcol] = c64{acc[r], acc[r + 1]};
-    for (int e = tid; e < B * 3 * B; e += 256) {
+    Wn[t0.crow][t0.col] = c64{u0[0], u0[1]};
+    Wn[t0.crow + 1][t0.col] = c64{u0[2], u0[3]};
+    Wn[t1.crow][t1.col] = c64{u1[0], u1[1]};
+    Wn[t1.crow + 1][t1.col] = c64{u1[2], u1[3]};
+    for (int e = tid; e < B * 3 * B; e += kBdLuThreads) {
       const int i = e / (3 * B), col = e - i * 3 * B;
       Wn[B + i][col] = Nx[i][col];
       if (col >= 2 * B) Wn[i][col] = c64{0.f, 0.f};
@@ -296,19 +397,25 @@ __global__ __launch_bounds__(256) void k_bd_lu(const BdProb* __restrict__ bp, co
 }
 
 // ---------------------------------------------------------------------------
-// Chunk solve: X = D_c^-1 (32 columns), one group of two waves per (node,
-// chunk, column tile), each wave 16 rows of the block.  rhs 0: the border's
-// columns (tile 0: the separator before the chunk, 1: the one after, then
-// f G), written to W; rhs 1: V, 2: R, written to X.  A block step is a chain
-// of five 32 x 32 products; each block's matrices are read from memory into
-// registers while the product before them runs.
+// Chunk solve: X = D_c^-1 (32 columns), one group of eight waves per (node,
+// chunk, column tile), each wave 8 rows x 16 columns of the block on
+// v_mfma_f32_16x16x4f32.  rhs 0: the border's columns (tile 0: the separator
+// before the chunk, 1: the one after, then f G), written to W; rhs 1: V, 2: R,
+// written to X.  A block step is a chain of five 32 x 32 products between
+// barriers, so a product is spread over all waves (512 cycles of matrix core
+// each) and the matrices of a step go through LDS, loaded a step before.  64
+// nodes of n = 4096, 32 columns: 0.20 ms, 6.5 us per block step (two waves,
+// operands from global memory: 0.45); the six tiles of W 0.80 ms (1.68).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(128) void k_bd_solve(const BdProb* __restrict__ bp, const int* __restrict__ prefix,
-                                                  int cnt, int total, const ProbDesc* __restrict__ pd, NodeArrays na,
-                                                  const c64* __restrict__ blocks,
-                                                  const unsigned char* __restrict__ perms, int rhs,
-                                                  const c128* __restrict__ Rb, c64* __restrict__ out,
-                                                  const int* __restrict__ conv) {
+constexpr int kBdSolveThreads = 512;
+
+__global__ __launch_bounds__(kBdSolveThreads) void k_bd_solve(const BdProb* __restrict__ bp,
+                                                              const int* __restrict__ prefix, int cnt, int total,
+                                                              const ProbDesc* __restrict__ pd, NodeArrays na,
+                                                              const c64* __restrict__ blocks,
+                                                              const unsigned char* __restrict__ perms, int rhs,
+                                                              const c128* __restrict__ Rb, c64* __restrict__ out,
+                                                              const int* __restrict__ conv) {
   const int v = xcd_remap(blockIdx.x, gridDim.x, total);
   if (v < 0) return;
   const int s = find_slot(prefix, cnt, v);
@@ -325,128 +432,127 @@ __global__ __launch_bounds__(128) void k_bd_solve(const BdProb* __restrict__ bp,
   const int st = bd_start(q, c), len = bd_start(q, c + 1) - 1 - st;
   const c128* __restrict__ f = na.fz + (long long)g * kMaxTerms;
   const int L = D.L, NL = D.N * L, n = D.n;
-  const int tid = threadIdx.x, wave = tid >> 6, rb = 16 * wave;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   __shared__ c64 T[2 * B][B + 1];  // right-hand side window
   __shared__ c64 X[3][B][B + 1];   // block solutions (backward: a ring of three)
-  __shared__ unsigned char perm[kBdMaxBlocks * 2 * B];
+  __shared__ c64 Ms[3][B][B + 1];  // the step's block matrices
+  __shared__ __align__(16) unsigned char perm[kBdMaxBlocks * 2 * B];
 
   const c64* __restrict__ bin = blocks + q.offB + ((long long)j * q.nb + st) * 5 * B2;
   const unsigned char* __restrict__ pin = perms + q.offPerm + ((long long)j * q.nb + st) * 2 * B;
   const int os = rhs == 0 ? q.wc : q.Lp;
   c64* __restrict__ o = out + (rhs == 0 ? q.offW : q.offX) + ((long long)j * q.nb + st) * B * os + tile * B;
 
-  auto rhs_elem = [&](int kb, int i, int col) -> c64 {
+  // right-hand side entry (row i of block kb, column tid % 32)
+  const int rc = tid & (B - 1), cc = tile * B + rc;
+  const c128 fh = rhs == 0 && tile >= 2 ? bd_lowrank_f(D, f, cc - 2 * B) : c128{0.0, 0.0};
+  auto rhs_elem = [&](int kb, int i) -> c64 {
     const int gr = (st + kb) * B + i;
     if (rhs == 0) {
-      if (tile == 0) return kb == 0 ? bd_elem(D, f, q.w, gr, (st - 1) * B + col) : c64{0.f, 0.f};
-      if (tile == 1) return kb == len - 1 ? bd_elem(D, f, q.w, gr, (st + len) * B + col) : c64{0.f, 0.f};
-      return bd_lowrank(D, f, gr, (tile - 2) * B + col);
+      if (tile == 0) return kb == 0 ? bd_elem(D, f, q.w, gr, (st - 1) * B + rc) : c64{0.f, 0.f};
+      if (tile == 1) return kb == len - 1 ? bd_elem(D, f, q.w, gr, (st + len) * B + rc) : c64{0.f, 0.f};
+      return bd_lowrank(fh, D.G32[(long long)gr * q.rp + cc - 2 * B]);
     }
-    const int cc = tile * B + col;
     if (gr >= n || cc >= L) return c64{0.f, 0.f};
     return to64(rhs == 1 ? D.V[(long long)cc * n + gr] : Rb[D.offY + (long long)gr * NL + (long long)j * L + cc]);
   };
-  const BdLane bl;
-  // this lane's row of a block matrix (its component is chosen when used)
-  auto load_a = [&](float4 (&a)[B / 2], const c64* m) {
-    const float4* p = reinterpret_cast<const float4*>(m + (rb + bl.arow) * B);
-#pragma unroll
-    for (int x = 0; x < B / 2; ++x) a[x] = p[x];
+  const BdTile tl((wave & 3) * 8, (wave >> 2) * 16);
+  const int crow = tl.crow, col = tl.col;
+  // a block matrix goes through registers (one 16-byte piece per thread, loaded
+  // a step before it is needed) into LDS: read as the operand's lanes need it,
+  // every entry would be fetched four times, 16 pieces per load instruction
+  static_assert(B2 * sizeof(c64) == kBdSolveThreads * sizeof(float4), "a block matrix is one piece per thread");
+  auto fetch = [&](int kb, int which) {
+    const int k = max(0, min(kb, len - 1));
+    return reinterpret_cast<const float4*>(bin + ((long long)k * 5 + which) * B2)[tid];
   };
-  auto mul = [&](const float4 (&a)[B / 2], const c64 (&b)[B][B + 1], float sign, floatx16 acc) {
-    const float sg = sign * bl.asign;
-#pragma unroll
-    for (int x = 0; x < B / 2; ++x) {
-      acc = bd_mfma(sg * (bl.acomp ? a[x].y : a[x].x), bd_comp(b[2 * x][bl.bcol], bl.bcomp), acc);
-      acc = bd_mfma(sg * (bl.acomp ? a[x].w : a[x].z), bd_comp(b[2 * x + 1][bl.bcol], bl.bcomp), acc);
-    }
-    return acc;
+  auto stage = [&](int slot, float4 m) {
+    c64* d = &Ms[slot][tid / (B / 2)][2 * (tid & (B / 2 - 1))];
+    d[0] = c64{m.x, m.y};
+    d[1] = c64{m.z, m.w};
   };
-  constexpr int PT = B2 / 128;  // right-hand side entries per thread
-  c64 nxt[PT];
-  for (int e = tid; e < 2 * B2; e += 128) {
-    const int i = e / B, col = e & (B - 1);
-    T[i][col] = i / B < len ? rhs_elem(i / B, i & (B - 1), col) : c64{0.f, 0.f};
+  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  constexpr int PT = B2 / kBdSolveThreads;  // right-hand side entries per thread and block
+  for (int e = tid; e < 2 * B2; e += kBdSolveThreads) {
+    const int i = e / B;
+    T[i][rc] = i / B < len ? rhs_elem(i / B, i & (B - 1)) : c64{0.f, 0.f};
   }
-  float4 a0[B / 2], a1[B / 2];
-  for (int e = tid; e < len * B / 2; e += 128)
+  for (int e = tid; e < len * B / 2; e += kBdSolveThreads)
     reinterpret_cast<unsigned*>(perm)[e] = reinterpret_cast<const unsigned*>(pin)[e];
-  load_a(a0, bin);
+  stage(0, fetch(0, 0));
+  stage(1, fetch(0, 1));
+  float4 pa = fetch(1, 0), pb = fetch(1, 1);
+  c64 nxt[PT];
+  auto load_rhs = [&](int kb) {
+#pragma unroll
+    for (int u = 0; u < PT; ++u)
+      nxt[u] = kb < len ? rhs_elem(kb, tid / B + u * (kBdSolveThreads / B)) : c64{0.f, 0.f};
+  };
+  load_rhs(2);
   __syncthreads();
   for (int k = 0; k < len; ++k) {  // forward
-    const bool more = k + 1 < len;
-    const c64* bk = bin + (long long)k * 5 * B2;
-    if (more) load_a(a1, bk + B2);
-#pragma unroll
-    for (int u = 0; u < PT; ++u) {
-      const int e = tid + 128 * u;
-      nxt[u] = k + 2 < len ? rhs_elem(k + 2, e / B, e & (B - 1)) : c64{0.f, 0.f};
-    }
-    // gather the pivot rows, then x_k = L11^-1 t
+    // x_k = L11^-1 t, its rows read through the pivot order
     const unsigned char* pk = perm + k * 2 * B;
-    c64 low[8];
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) low[r / 2] = T[pk[B + rb + bl.crow(r)]][bl.bcol];
-    for (int e = tid; e < B2; e += 128) X[2][e / B][e & (B - 1)] = T[pk[e / B]][e & (B - 1)];
+    const uint4 pr = *reinterpret_cast<const uint4*>(pk + tl.kh * (B / 2));
+    const unsigned pw[4] = {pr.x, pr.y, pr.z, pr.w};
+    floatx4 acc = tl.mul<B>(Ms[0], 1.f, zero, [&](int x) {
+      const int y = x & (B / 2 - 1);
+      return T[(pw[y >> 2] >> (8 * (y & 3))) & 63u][col];
+    });
+    const c64 lo0 = T[pk[B + crow]][col], lo1 = T[pk[B + crow + 1]][col];
+    X[0][crow][col] = c64{acc[0], acc[1]};
+    X[0][crow + 1][col] = c64{acc[2], acc[3]};
+    o[((long long)k * B + crow) * os + col] = c64{acc[0], acc[1]};
+    o[((long long)k * B + crow + 1) * os + col] = c64{acc[2], acc[3]};
     __syncthreads();
-    floatx16 acc = mul(a0, X[2], 1.f, bd_zero());
+    if (k + 1 < len) {
+      stage(0, pa);  // every wave is done with L11^-1
+      pa = fetch(k + 2, 0);
+      acc = tl.mul<B>(Ms[1], -1.f, floatx4{lo0.re, lo0.im, lo1.re, lo1.im}, [&](int x) { return X[0][x][col]; });
+      T[crow][col] = c64{acc[0], acc[1]};
+      T[crow + 1][col] = c64{acc[2], acc[3]};
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int i = rb + bl.crow(r);
-      const c64 x = {acc[r], acc[r + 1]};
-      X[0][i][bl.bcol] = x;
-      o[((long long)k * B + i) * os + bl.bcol] = x;
-    }
-    if (more) load_a(a0, bk + 5 * B2);
-    __syncthreads();
-    if (more) {
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        acc[r] = low[r / 2].re;
-        acc[r + 1] = low[r / 2].im;
-      }
-      acc = mul(a1, X[0], -1.f, acc);
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) T[rb + bl.crow(r)][bl.bcol] = c64{acc[r], acc[r + 1]};
-#pragma unroll
-      for (int u = 0; u < PT; ++u) {
-        const int e = tid + 128 * u;
-        T[B + e / B][e & (B - 1)] = nxt[u];
-      }
+      for (int u = 0; u < PT; ++u) T[B + tid / B + u * (kBdSolveThreads / B)][rc] = nxt[u];
+      load_rhs(k + 3);
       __syncthreads();
+      stage(1, pb);  // read after the next step's barrier
+      pb = fetch(k + 2, 1);
     }
   }
   // backward: x_k = U11^-1 (x_k - U12 [x_{k+1}; x_{k+2}]), ring slot k % 3
   auto& S0 = *reinterpret_cast<c64(*)[B][B + 1]>(&T[0]);
+  stage(0, fetch(len - 1, 2));  // U11^-1; the U12 blocks of the last block are not used
+  float4 pi = fetch(len - 2, 2);
+  pa = fetch(len - 2, 3);
+  pb = fetch(len - 2, 4);
+  c64 xf0, xf1;
+  auto load_x = [&](int kb) {  // written by this lane in the forward sweep
+    const int k = max(kb, 0);
+    xf0 = o[((long long)k * B + crow) * os + col];
+    xf1 = o[((long long)k * B + crow + 1) * os + col];
+  };
+  load_x(len - 1);
   for (int k = len - 1; k >= 0; --k) {
-    const c64* bk = bin + (long long)k * 5 * B2;
-    float4 ua[B / 2], ub[B / 2];
-    if (k + 1 < len) load_a(ua, bk + 3 * B2);
-    if (k + 2 < len) load_a(ub, bk + 4 * B2);
-    load_a(a0, bk + 2 * B2);
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      // written by this lane in the forward sweep
-      const c64 x = o[((long long)k * B + rb + bl.crow(r)) * os + bl.bcol];
-      acc[r] = x.re;
-      acc[r + 1] = x.im;
-    }
-    if (k + 1 < len) acc = mul(ua, X[(k + 1) % 3], -1.f, acc);
-    if (k + 2 < len) acc = mul(ub, X[(k + 2) % 3], -1.f, acc);
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) S0[rb + bl.crow(r)][bl.bcol] = c64{acc[r], acc[r + 1]};
+    floatx4 acc = {xf0.re, xf0.im, xf1.re, xf1.im};
+    load_x(k - 1);
+    if (k + 2 < len) acc = tl.mul<B>(Ms[2], -1.f, acc, [&](int x) { return X[(k + 2) % 3][x][col]; });
+    if (k + 1 < len) acc = tl.mul<B>(Ms[1], -1.f, acc, [&](int x) { return X[(k + 1) % 3][x][col]; });
+    S0[crow][col] = c64{acc[0], acc[1]};
+    S0[crow + 1][col] = c64{acc[2], acc[3]};
     __syncthreads();
-    acc = mul(a0, S0, 1.f, bd_zero());
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const int i = rb + bl.crow(r);
-      const c64 x = {acc[r], acc[r + 1]};
-      X[k % 3][i][bl.bcol] = x;
-      o[((long long)k * B + i) * os + bl.bcol] = x;
-    }
+    stage(1, pa);
+    stage(2, pb);
+    pa = fetch(k - 2, 3);
+    pb = fetch(k - 2, 4);
+    acc = tl.mul<B>(Ms[0], 1.f, zero, [&](int x) { return S0[x][col]; });
+    X[k % 3][crow][col] = c64{acc[0], acc[1]};
+    X[k % 3][crow + 1][col] = c64{acc[2], acc[3]};
+    o[((long long)k * B + crow) * os + col] = c64{acc[0], acc[1]};
+    o[((long long)k * B + crow + 1) * os + col] = c64{acc[2], acc[3]};
     __syncthreads();
+    stage(0, pi);  // read after the next step's first barrier
+    pi = fetch(k - 2, 2);
   }
 }
 
@@ -476,6 +582,7 @@ __global__ __launch_bounds__(256) void k_bd_hprod(const BdProb* __restrict__ bp,
   const int st = bd_start(q, c), len = bd_start(q, c + 1) - 1 - st;
   __shared__ float Hs[B][128 + 4];
   __shared__ float Zs[B][2 * B + 4];
+  const float* __restrict__ H = D.H32 + (long long)st * B * q.rp;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const c64* __restrict__ Z = Zb + (rhs == 0 ? q.offW : q.offX) + ((long long)j * q.nb + st) * B * os + tile * B;
   floatx16 acc[2] = {bd_zero(), bd_zero()};
@@ -485,8 +592,8 @@ __global__ __launch_bounds__(256) void k_bd_hprod(const BdProb* __restrict__ bp,
   auto load = [&](int k) {
 #pragma unroll
     for (int u = 0; u < HU; ++u) {
-      const int e = tid + 256 * u;
-      hr[u] = bd_h(D, (st + k) * B + e / 128, h0 + (e & 127));
+      const int e = tid + 256 * u, h = h0 + (e & 127);
+      hr[u] = h < q.rp ? H[(long long)(k * B + e / 128) * q.rp + h] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < ZU; ++u) {
@@ -574,7 +681,7 @@ __global__ __launch_bounds__(256) void k_bd_border(const BdProb* __restrict__ bp
         if (sc == grp) c1 = m;
         if (sc == grp + 1) c1 = B + m;
       } else {
-        x = bd_lowrank(D, f, sb * B + i, col - low0);
+        x = bd_lowrank(bd_lowrank_f(D, f, col - low0), D.G32[(long long)(sb * B + i) * q.rp + col - low0]);
         c0 = c1 = 2 * B + col - low0;
       }
       if (c0 >= 0)
@@ -593,7 +700,7 @@ __global__ __launch_bounds__(256) void k_bd_border(const BdProb* __restrict__ bp
     c64 x = {0.f, 0.f};
     if (col < low0) {
       const int sc = col / B, m = col & (B - 1);
-      x.re = bd_h(D, (bd_start(q, sc + 1) - 1) * B + m, h);
+      x.re = D.H32[(long long)((bd_start(q, sc + 1) - 1) * B + m) * q.rp + h];
       x = x - pe(sc, B + m);   // the separator after chunk sc
       x = x - pe(sc + 1, m);   // and before chunk sc + 1
     } else {
@@ -641,10 +748,15 @@ __global__ __launch_bounds__(256) void k_bd_rhs(const BdProb* __restrict__ bp, c
 
 // ---------------------------------------------------------------------------
 // y = x - W [y_S; s] on the interior blocks, y_S on the separators; Y = y or
-// Y += y, with the column maxima.  One group of two waves per (node, block,
-// column tile), each wave 16 rows; the border's solution is staged in LDS.
+// Y += y, with the column maxima.  One group of eight waves per (node, chunk
+// with the separator after it, column tile): the border's solution is staged
+// in LDS once, each wave takes 16-row strips of W in turn, the next 32
+// columns of a strip in flight while one runs on the matrix cores.  Bound by
+// reading W and by its products alike.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(128) void k_bd_apply(const BdProb* __restrict__ bp, const int* __restrict__ prefix,
+constexpr int kBdMaxTiles = 2 + kBdMaxRank / B;
+
+__global__ __launch_bounds__(512) void k_bd_apply(const BdProb* __restrict__ bp, const int* __restrict__ prefix,
                                                   int cnt, int total, const ProbDesc* __restrict__ pd, int add,
                                                   const c64* __restrict__ Wb, const c64* __restrict__ Xb,
                                                   const c128* __restrict__ YS, c128* __restrict__ Yb,
@@ -656,69 +768,86 @@ __global__ __launch_bounds__(128) void k_bd_apply(const BdProb* __restrict__ bp,
   const ProbDesc& D = pd[q.prob];
   const int tiles = q.Lp / B, L = D.L, NL = D.N * L, n = D.n, ns = q.nch - 1;
   int t = v - prefix[s];
-  const int j = t / (q.nb * tiles);
-  t -= j * q.nb * tiles;
-  const int blk = t / tiles, tile = t - blk * tiles;
+  const int j = t / (q.nch * tiles);
+  t -= j * q.nch * tiles;
+  const int c = t / tiles, tile = t - c * tiles;
   const int g = D.node0 + j;
   if (conv != nullptr && conv[g]) return;
-  const int tid = threadIdx.x, wave = tid >> 6, rb = 16 * wave;
+  const int st = bd_start(q, c), len = bd_start(q, c + 1) - 1 - st;
+  const int tid = threadIdx.x, wave = tid >> 6;
   const BdLane bl;
   const int cc = tile * B + bl.bcol;
-  int c = 0;
-  while (blk > bd_start(q, c + 1) - 1) ++c;  // the chunk, or the separator after it
-  const bool sep = blk == bd_start(q, c + 1) - 1;
   const c128* __restrict__ ys = YS + q.offYS + (long long)j * L;
-  __shared__ c64 Sv[B][B + 1];
-  floatx16 acc;
-  if (sep) {
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-      const c128 x = cc < L ? ys[(long long)(c * B + rb + bl.crow(r)) * NL + cc] : c128{0.0, 0.0};
-      acc[r] = float(x.re);
-      acc[r + 1] = float(x.im);
+  // the border rows that W's column tiles multiply (0 and 1: the separators
+  // before and after, where there are such)
+  __shared__ c64 Sv[kBdMaxTiles][B][B + 1];
+  __shared__ c64 Wt[8][16][B + 1];  // per wave: a strip's 32 columns of W
+  const int nk = q.wc / B, nt = nk - (c == 0) - (c == ns);  // tiles that exist
+  auto kt_of = [&](int i) {
+    i += c == 0 ? 1 : 0;
+    return c == ns && i >= 1 ? i + 1 : i;
+  };
+  for (int e = tid; e < nk * B2; e += 512) {
+    const int kt = e / B2, i = (e / B) & (B - 1), m = e & (B - 1), col = tile * B + m;
+    const int row = kt == 0 ? (c - 1) * B : kt == 1 ? c * B : ns * B + (kt - 2) * B;
+    const bool none = (kt == 0 && c == 0) || (kt == 1 && c == ns) || col >= L;
+    Sv[kt][i][m] = none ? c64{0.f, 0.f} : to64(ys[(long long)(row + i) * NL + col]);
+  }
+  __syncthreads();
+  double m2 = 0.0;
+  auto put = [&](int gr, c64 x) {
+    if (gr < n && cc < L) {
+      c128* __restrict__ Y = Yb + D.offY + (long long)gr * NL + (long long)j * L + cc;
+      c128 y = to128(x);
+      if (add) y = *Y + y;
+      *Y = y;
+      m2 = nanmax(m2, norm2(y));
     }
-  } else {
-    const c64* __restrict__ X = Xb + q.offX + ((long long)j * q.nb + blk) * B * q.Lp + tile * B;
+  };
+  for (int strip = wave; strip < 2 * len; strip += 8) {
+    const long long r0 = (long long)j * q.nb * B + st * B + strip * 16;
+    const c64* __restrict__ X = Xb + q.offX + r0 * q.Lp + tile * B;
+    // (16 bytes per lane and load, four lanes per row and 64-byte piece)
+    const int lane = tid & 63, wrow = lane >> 2, wp = lane & 3;
+    const float4* __restrict__ W = reinterpret_cast<const float4*>(Wb + q.offW + (r0 + wrow) * q.wc);
+    floatx16 acc;
+    float4 w4[4];
+    auto load = [&](int i) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w4[x] = W[kt_of(i) * (B / 2) + 4 * x + wp];
+    };
+    if (nt > 0) load(0);
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
-      const c64 x = X[(long long)(rb + bl.crow(r)) * q.Lp + bl.bcol];
+      const c64 x = X[(long long)bl.crow(r) * q.Lp + bl.bcol];
       acc[r] = x.re;
       acc[r + 1] = x.im;
     }
-    const c64* __restrict__ W = Wb + q.offW + (((long long)j * q.nb + blk) * B + rb + bl.arow) * q.wc;
-    for (int kt = 0; kt < q.wc / B; ++kt) {
-      if ((kt == 0 && c == 0) || (kt == 1 && c == ns)) continue;  // uniform
-      const int row0 = kt == 0 ? (c - 1) * B : kt == 1 ? c * B : ns * B + (kt - 2) * B;
-      float4 a[B / 2];
+#pragma unroll 1
+    for (int i = 0; i < nt; ++i) {
+      // (a wave's own LDS traffic is in order: no barrier)
 #pragma unroll
-      for (int x = 0; x < B / 2; ++x) a[x] = reinterpret_cast<const float4*>(W + kt * B)[x];
-      __syncthreads();
-      for (int e = tid; e < B2; e += 128) {
-        const int col = tile * B + (e & (B - 1));
-        Sv[e / B][e & (B - 1)] = col < L ? to64(ys[(long long)(row0 + e / B) * NL + col]) : c64{0.f, 0.f};
+      for (int x = 0; x < 4; ++x) {
+        Wt[wave][wrow][8 * x + 2 * wp] = c64{w4[x].x, w4[x].y};
+        Wt[wave][wrow][8 * x + 2 * wp + 1] = c64{w4[x].z, w4[x].w};
       }
-      __syncthreads();
-#pragma unroll
-      for (int x = 0; x < B / 2; ++x) {
-        acc = bd_mfma(-bl.asign * (bl.acomp ? a[x].y : a[x].x), bd_comp(Sv[2 * x][bl.bcol], bl.bcomp), acc);
-        acc = bd_mfma(-bl.asign * (bl.acomp ? a[x].w : a[x].z), bd_comp(Sv[2 * x + 1][bl.bcol], bl.bcomp), acc);
-      }
+      __builtin_amdgcn_wave_barrier();
+      if (i + 1 < nt) load(i + 1);
+      const c64(&S)[B][B + 1] = Sv[kt_of(i)];
+#pragma unroll 8
+      for (int x = 0; x < B; ++x)
+        acc = bd_mfma(-bl.asign * bd_comp(Wt[wave][bl.arow][x], bl.acomp), bd_comp(S[x][bl.bcol], bl.bcomp), acc);
+      __builtin_amdgcn_wave_barrier();
     }
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) put(st * B + strip * 16 + bl.crow(r), c64{acc[r], acc[r + 1]});
   }
-  double m2 = 0.0;
-  if (cc < L) {
-    c128* __restrict__ Y = Yb + D.offY + (long long)j * L + cc;
+  if (c < ns && wave < 2)  // the separator: 16 rows per wave
 #pragma unroll
     for (int r = 0; r < 16; r += 2) {
-      const int gr = blk * B + rb + bl.crow(r);
-      if (gr < n) {
-        c128 y = {double(acc[r]), double(acc[r + 1])};
-        if (add) y = Y[(long long)gr * NL] + y;
-        Y[(long long)gr * NL] = y;
-        m2 = nanmax(m2, norm2(y));
-      }
+      const int i = 16 * wave + bl.crow(r);
+      put((st + len) * B + i, Sv[1][i][bl.bcol]);
     }
-  }
   m2 = nanmax(m2, __shfl_xor(m2, 32, 64));
   if ((threadIdx.x & 63) < 32 && cc < L)
     atomicMax(&ir.ynorm[(long long)g * kNormStride + cc], (unsigned long long)__double_as_longlong(sqrt(m2)));
@@ -803,7 +932,7 @@ void bd_tables(BdTables& bt, std::vector<int>& buf, const std::vector<BdProb>& b
     hv.push_back(N * q.nch * tl * hb);
     bo.push_back(N * (q.nch - 1 + q.rp / B));
     rh.push_back(N * ceil_div(q.b * L, 256));
-    ap.push_back(N * q.nb * tl);
+    ap.push_back(N * q.nch * tl);
     nd.push_back(N);
   }
   build_prefix(buf, bt.lu, lu);
@@ -819,9 +948,9 @@ void bd_tables(BdTables& bt, std::vector<int>& buf, const std::vector<BdProb>& b
 
 hipError_t bd_factor(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const NodeArrays& na,
                      const BdBufs& m, int* info, hipStream_t st) {
-  hipLaunchKernelGGL(k_bd_lu, dim3(bt.lu.total), dim3(256), 0, st, bp, pre + bt.lu.off, bt.lu.cnt, pd, na, m.blocks,
+  hipLaunchKernelGGL(k_bd_lu, dim3(bt.lu.total), dim3(kBdLuThreads), 0, st, bp, pre + bt.lu.off, bt.lu.cnt, pd, na, m.blocks,
                      m.perms, m.pivots, info);
-  hipLaunchKernelGGL(k_bd_solve, dim3(xcd_grid(bt.solve_e.total)), dim3(128), 0, st, bp, pre + bt.solve_e.off,
+  hipLaunchKernelGGL(k_bd_solve, dim3(xcd_grid(bt.solve_e.total)), dim3(kBdSolveThreads), 0, st, bp, pre + bt.solve_e.off,
                      bt.solve_e.cnt, bt.solve_e.total, pd, na, m.blocks, m.perms, 0, (const c128*)nullptr, m.W,
                      (const int*)nullptr);
   if (bt.hprod_e.total > 0)
@@ -836,7 +965,7 @@ hipError_t bd_factor(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, c
 hipError_t bd_solve_pre(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const NodeArrays& na,
                         const BdBufs& m, const c128* R, bool refine, const int* conv, hipStream_t st) {
   const int rhs = refine ? 2 : 1;
-  hipLaunchKernelGGL(k_bd_solve, dim3(xcd_grid(bt.solve_v.total)), dim3(128), 0, st, bp, pre + bt.solve_v.off,
+  hipLaunchKernelGGL(k_bd_solve, dim3(xcd_grid(bt.solve_v.total)), dim3(kBdSolveThreads), 0, st, bp, pre + bt.solve_v.off,
                      bt.solve_v.cnt, bt.solve_v.total, pd, na, m.blocks, m.perms, rhs, R, m.X, conv);
   if (bt.hprod_v.total > 0)
     hipLaunchKernelGGL(k_bd_hprod, dim3(xcd_grid(bt.hprod_v.total)), dim3(256), 0, st, bp, pre + bt.hprod_v.off,
@@ -849,7 +978,7 @@ hipError_t bd_solve_pre(const BdTables& bt, const BdProb* bp, const ProbDesc* pd
 
 hipError_t bd_solve_post(const BdTables& bt, const BdProb* bp, const ProbDesc* pd, const int* pre, const BdBufs& m,
                          c128* Y, bool refine, const int* conv, IrState ir, hipStream_t st) {
-  hipLaunchKernelGGL(k_bd_apply, dim3(xcd_grid(bt.apply.total)), dim3(128), 0, st, bp, pre + bt.apply.off,
+  hipLaunchKernelGGL(k_bd_apply, dim3(xcd_grid(bt.apply.total)), dim3(512), 0, st, bp, pre + bt.apply.off,
                      bt.apply.cnt, bt.apply.total, pd, refine ? 1 : 0, m.W, m.X, m.YS, Y, conv, ir);
   return hipGetLastError();
 }

@@ -54,7 +54,7 @@ struct ProbDesc {
   int a_bw[kMaxTerms];             // real banded A_i (half-bandwidth, 0: not banded): the
                                    // real-term residual runs over the band's k only
   int a_lr[kMaxTerms];             // real low-rank A_i = G H^T (rank, 0: not factored):
-  const double *LrG[kMaxTerms], *LrH[kMaxTerms];  // the real-term residual applies G (H^T Y), with
+  const double* LrG[kMaxTerms];    // the real-term residual applies G (H^T Y), with
   c128* LrZ[kMaxTerms];            // Z = H^T Y (rank x N*L) formed before it
   const c128* V;          // caller probes, column-major n x L
   c128* S;                // caller moments, column-major n x L x KK
@@ -64,7 +64,8 @@ struct ProbDesc {
   int active;             // 0: the problem sits out this pass on resident factors (its
                           // nodes count as converged, its V and S are not touched)
   int band;               // 0: dense factors; else the band path's window half-width (1, 2 or 4)
-  int bordered;           // 1: takes the bordered path
+  int bordered;           // 1: takes the bordered path, with
+  const float *G32, *H32; // the low-rank factors side by side (rows and columns padded to blocks)
   long long offF, offP;   // its factor (elements) and pivot bytes
   const c128* fpts;       // with zpts: given coefficients in place of f_i(z_j), at
                           // fpts[j*ell + i] (device), or nullptr

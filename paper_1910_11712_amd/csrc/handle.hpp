@@ -22,6 +22,7 @@ struct Split {
   std::unique_ptr<DevMem> mats[kMaxTerms];
   std::unique_ptr<DevMem> diags[kMaxTerms];
   std::unique_ptr<DevMem> lrG[kMaxTerms], lrH[kMaxTerms];
+  DevMem lr32;  // every low-rank G, then every H, side by side in FP32
   DevMem norms, fn_nodes, fn_coef, fn_roots;
   std::unique_ptr<MomentsPlan> plan;  // resident factors of the last call
   std::shared_ptr<ExtractWork> xw;

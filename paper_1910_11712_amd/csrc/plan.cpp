@@ -327,7 +327,7 @@ nep_status MomentsPlan::bordered_factor(hipStream_t st) {
   NEP_HIP(lu_run<float>(lub_, dmdb_.as<MatDesc>(), dlub_prefix_.as<int>(), bd_.S, drowsb_.as<int>(),
                         drowsb_snap_.as<int>(), rowsb_total_, dinfob_.as<int>(), nullptr, dlinvb_.as<c64>(),
                         ddinvb_.as<c64>(), ddinvb_off_.as<long long>(), darriveb_.as<int>(), st,
-                        st == beside_ ? LuStreams{} : ls_));  // (ls_ belongs to the dense LU there)
+                        beside_ != nullptr && st == beside_ ? LuStreams{} : ls_));  // (ls_ is the dense LU's there)
   NEP_HIP(bd_pivots(bdt_, dbp_.as<BdProb>(), pd, pre, bd_, drowsb_.as<int>(), dpmin_.as<double>(), nullptr, nnodes,
                     st));
   return NEP_OK;
@@ -381,7 +381,6 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
       const int rk = (i < q.op->ell && !q.op->a_cplx) ? q.op->lr_rank[i] : 0;
       D.a_lr[i] = rk;
       D.LrG[i] = rk > 0 ? q.op->dLrG[i] : nullptr;
-      D.LrH[i] = rk > 0 ? q.op->dLrH[i] : nullptr;
       D.LrZ[i] = rk > 0 ? dlrz_.as<c128>() + zoff : nullptr;
       if (rk > 0) {
         int S, srows;
@@ -407,6 +406,8 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
       D.a_bw[i] = i < q.op->ell ? q.op->band_w[i] : 0;
       D.fn_root[i] = i < q.op->ell ? q.op->fn_root[i] : 0;
     }
+    D.G32 = q.op->dG32;
+    D.H32 = q.op->dH32;
     D.normA = q.op->dnormA;
     D.fn_nodes = q.op->dfn_nodes;
     D.fn_coef = q.op->dfn_coef;

@@ -82,6 +82,7 @@ struct SplitOperator {
   int lr_rank[kMaxTerms] = {0};
   const double* dLrG[kMaxTerms] = {nullptr};
   const double* dLrH[kMaxTerms] = {nullptr};
+  const float *dG32 = nullptr, *dH32 = nullptr;  // all of them side by side, FP32, padded to blocks of kBdBlk
   const double* dnormA = nullptr;
   std::vector<double> normA;
   const FnNode* dfn_nodes = nullptr;
