@@ -108,13 +108,14 @@ struct SolvePlan {
   int rpt = 1;      // rows per thread of the 512-thread solve groups (n <= 512 * rpt)
   int nbig = 0;     // matrices of more than 512 rows (the first nbig in sorted order)
   int nmid = 0;     // then matrices of 257..512 rows; the rest have at most 256
-  // the large matrices as paired 256-thread groups (complex FP32, lg <= 8,
-  // rpt <= 2): -1 when they make 2048 groups or more, 0 never, 1 always
+  int nhuge = 0;    // matrices of more than 1024 rows (FP64 ones take k_trsv)
+  // -1: k_trsm; else k_trsv with lg columns per group, and the large matrices
+  // (complex FP32, lg <= 8, rpt <= 2) as paired 256-thread groups (1) or not (0)
   int paired = -1;
   // complex FP32: the first nblk matrices (at least kSolveBlockedMinN rows)
   // take the blocked solve (solve_blk.hip) over big blocks of nbk rows, with
   // right-hand sides in the work buffer W (npad x L complex FP32 per matrix,
-  // npad the largest n rounded up to 64); the rest take k_trsv
+  // npad the largest n rounded up to 64); the rest take k_trsm or k_trsv
   int nblk = 0, nbk = 256, npad = 0, L = 0;
   c64* W = nullptr;
 };

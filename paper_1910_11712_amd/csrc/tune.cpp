@@ -1,9 +1,10 @@
 // Autotuner of launch shapes.  A moments plan has a few launch-shape choices
 // whose best setting depends on the batch (how many matrices of which sizes)
 // and on the device rather than on the arithmetic:
-//   * the width of the triangular solves' column groups (4, 8 or 16 right-hand
-//     columns per work-group): fewer, wider groups re-read each factor less,
-//     more, narrower groups fill more CUs when there are few matrices;
+//   * the triangular solves: on the matrix cores (built in), or on the vector
+//     units with 4, 8 or 16 right-hand columns per work-group (fewer, wider
+//     groups re-read each factor less, more, narrower groups fill more CUs
+//     when there are few matrices), there also
 //   * paired 256-thread solve groups (two per CU) for the large matrices,
 //     which cover each other's barrier waits when there are many of them;
 //   * 256-thread panel groups for panels of at most 256 rows (two per CU)
@@ -15,7 +16,8 @@
 //   * the LU's panel width, 64 or 128: wider panels give the trailing update
 //     twice the products per C byte but lengthen the panel chain.
 // Every setting computes the moments to the same accuracy; all but the panel
-// width give the same bits (the panel width changes the factors' rounding).
+// width and the matrix-core solve give the same bits (the width changes the
+// factors' rounding, the matrix cores the order of the solve's sums).
 // The tuner times each candidate with full moment passes on the plan's own
 // buffers (HIP events on the caller's stream, median of a few passes), keeps
 // the fastest if it beats the built-in setting by more than 2% (the built-in
@@ -54,12 +56,12 @@ TuneState& tune_state() {
   return s;
 }
 
-// 1 when the large matrices run as paired groups under knobs k
-int eff_paired(const SolvePlan& sp, int prec, const MomentsPlan::Knobs& k, int L) {
+// -1: the matrix-core solve; 1 when the large matrices run as paired groups
+// of the other under knobs k
+int eff_paired(const SolvePlan& sp, int prec, const MomentsPlan::Knobs& k) {
   const bool can = prec == NEP_PREC_C32_IR64 && k.lg <= 8 && sp.rpt <= 2 && sp.nbig > 0;
-  if (!can) return 0;
-  if (k.paired >= 0) return k.paired;
-  return (long long)sp.nbig * ceil_div(L, k.lg) >= 2048 ? 1 : 0;
+  if (k.paired < 0) return -1;
+  return can ? k.paired : 0;
 }
 
 }  // namespace
@@ -129,14 +131,14 @@ void MomentsPlan::candidates(std::vector<Knobs>& lu, std::vector<Knobs>& solve) 
         lu.push_back(k);
       }
   }
-  std::vector<std::pair<int, int>> seen{{base.lg, eff_paired(sp_, opt.prec, base, opt.L)}};
+  std::vector<std::pair<int, int>> seen{{base.lg, eff_paired(sp_, opt.prec, base)}};
   for (int lg : {4, 8, 16}) {
     if (!solve_lg_fits(sp_, lg, opt.L, opt.prec)) continue;
     for (int pr : {0, 1}) {
       Knobs k = base;
       k.lg = lg;
       k.paired = pr;
-      const std::pair<int, int> e{lg, eff_paired(sp_, opt.prec, k, opt.L)};
+      const std::pair<int, int> e{lg, eff_paired(sp_, opt.prec, k)};
       if (std::find(seen.begin(), seen.end(), e) != seen.end()) continue;
       seen.push_back(e);
       solve.push_back(k);
