@@ -93,7 +93,7 @@ struct IrState {
   int* conv;                  // 1 when converged (skip further work)
   int* stalled;               // 1 when the residual stopped decreasing
   int* sweeps;                // sweeps run per node
-  int* counters;              // [0] unconverged, [1] bad fn, [2] spare, [3] first bad node
+  int* counters;              // [0] unconverged, [1] bad fn, [2] k_ir_control's own, [3] first bad node
 };
 
 // Launch tables of a batch (host copies; uploaded into one device buffer).

@@ -446,17 +446,19 @@ hipError_t resid_run(const ProbDesc* pd, const int* prefix, const Table& t, cons
 }
 
 // ---------------------------------------------------------------------------
-// One group over every node: the unconverged count is reduced in LDS and
-// stored once, so the counter needs no clearing launch before the sweep.
-constexpr int kIrControlThreads = 1024;
+// One wave per node, a column per lane.  Each group adds its unconverged nodes
+// and itself to one word (counters[2], zero between launches); the group that
+// completes it stores the total, so that the counter needs no clearing launch
+// before the sweep.  (One group over all nodes, a node per thread: 19 us for 64
+// nodes of 32 columns and 240 us for 8192 of 8, in chains of dependent loads.)
+constexpr int kIrControlWaves = 4, kIrControlGroups = 1024, kIrCountBits = 21;
 
 __device__ __forceinline__ bool ir_control_node(const ProbDesc* __restrict__ pd, const NodeArrays& na,
                                                 const IrState& ir, int g, int sweep, double tol) {
-  const int p = na.prob[g];
-  const ProbDesc& D = pd[p];
+  const int p = na.prob[g], lane = threadIdx.x & 63;
   const double fn = na.fnorm[g];
   double rho = 0.0;
-  for (int c = 0; c < D.L; ++c) {
+  for (int c = lane; c < pd[p].L; c += 64) {
     const double rn = __longlong_as_double((long long)ir.rnorm[(long long)g * kNormStride + c]);
     const double yn = __longlong_as_double((long long)ir.ynorm[(long long)g * kNormStride + c]);
     const double den = fn * yn + ir.vnorm[p * 64 + c];
@@ -468,6 +470,8 @@ __device__ __forceinline__ bool ir_control_node(const ProbDesc* __restrict__ pd,
     ir.rnorm[(long long)g * kNormStride + c] = 0ull;
     ir.ynorm[(long long)g * kNormStride + c] = 0ull;
   }
+  for (int o = 32; o >= 1; o >>= 1) rho = fmax(rho, __shfl_xor(rho, o, 64));
+  if (lane > 0) return false;
   const double prev = ir.rho[g];
   ir.rho[g] = rho;
   ir.sweeps[g] = sweep + 1;
@@ -483,17 +487,24 @@ __device__ __forceinline__ bool ir_control_node(const ProbDesc* __restrict__ pd,
   return true;
 }
 
-__global__ __launch_bounds__(kIrControlThreads) void k_ir_control(const ProbDesc* __restrict__ pd, NodeArrays na,
-                                                                   IrState ir, int nnodes, int sweep, double tol) {
+__global__ __launch_bounds__(64 * kIrControlWaves) void k_ir_control(const ProbDesc* __restrict__ pd, NodeArrays na,
+                                                                     IrState ir, int nnodes, int sweep, double tol) {
   __shared__ int unconv;
   if (threadIdx.x == 0) unconv = 0;
   __syncthreads();
   int mine = 0;
-  for (int g = threadIdx.x; g < nnodes; g += blockDim.x)
+  for (int g = blockIdx.x * kIrControlWaves + (threadIdx.x >> 6); g < nnodes; g += gridDim.x * kIrControlWaves)
     if (!ir.conv[g] && ir_control_node(pd, na, ir, g, sweep, tol)) ++mine;
   if (mine > 0) atomicAdd(&unconv, mine);
   __syncthreads();
-  if (threadIdx.x == 0) ir.counters[0] = unconv;
+  if (threadIdx.x == 0) {
+    const unsigned add = (1u << kIrCountBits) | (unsigned)unconv;
+    const unsigned sum = atomicAdd(reinterpret_cast<unsigned*>(ir.counters) + 2, add) + add;
+    if (sum >> kIrCountBits == gridDim.x) {
+      ir.counters[0] = (int)(sum & ((1u << kIrCountBits) - 1));
+      ir.counters[2] = 0;
+    }
+  }
 }
 
 __global__ void k_ir_reset(IrState ir, int nnodes) {
@@ -518,8 +529,9 @@ __global__ void k_ir_reset(IrState ir, int nnodes) {
 
 hipError_t ir_control(const ProbDesc* pd, const NodeArrays& na, IrState ir, int nnodes, int sweep, double tol,
                       hipStream_t st) {
-  const int nt = std::min(kIrControlThreads, std::max(64, ceil_div(nnodes, 64) * 64));
-  hipLaunchKernelGGL(k_ir_control, dim3(1), dim3(nt), 0, st, pd, na, ir, nnodes, sweep, tol);
+  if (nnodes >= 1 << kIrCountBits) return hipErrorInvalidValue;
+  const int groups = std::max(1, std::min(kIrControlGroups, ceil_div(nnodes, kIrControlWaves)));
+  hipLaunchKernelGGL(k_ir_control, dim3(groups), dim3(64 * kIrControlWaves), 0, st, pd, na, ir, nnodes, sweep, tol);
   return hipGetLastError();
 }
 
