@@ -66,6 +66,28 @@ constexpr double kNlTie = 1e-10;   // relative tie window of the greedy selectio
 constexpr double kNlDep = 1e-12;   // a new vector this small after Gram--Schmidt
                                    // (relative) does not extend U
 
+// Returned pairs by ascending real part, then imaginary part.  The two of a
+// conjugate pair have real parts that differ by rounding alone, so equal means
+// equal up to kNlTie there: such neighbours go by their imaginary parts.
+template <typename F>
+void order_pairs(std::vector<int>& v, F&& lam) {
+  std::sort(v.begin(), v.end(), [&](int x, int y) {
+    const auto lx = lam(x), ly = lam(y);
+    return lx.real() != ly.real() ? lx.real() < ly.real() : lx.imag() < ly.imag();
+  });
+  for (size_t pass = 0, moved = 1; moved != 0 && pass < v.size(); ++pass) {
+    moved = 0;
+    for (size_t i = 0; i + 1 < v.size(); ++i) {
+      const auto a = lam(v[i]), b = lam(v[i + 1]);
+      const double tie = kNlTie * std::abs(a);
+      if (std::abs(a.real() - b.real()) <= tie && a.imag() - b.imag() > tie) {
+        std::swap(v[i], v[i + 1]);
+        moved = 1;
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Device kernels
 // ---------------------------------------------------------------------------
@@ -77,6 +99,15 @@ __device__ __forceinline__ c128 wave_sum(c128 v) {
   }
   return v;
 }
+
+// Sum over every four lanes (quad permutations: no LDS).
+__device__ __forceinline__ double quad_sum(double v) {
+  v += __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, true),
+                        __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, true));
+  return v + __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x4E, 0xF, 0xF, true),
+                              __builtin_amdgcn_mov_dpp(__double2loint(v), 0x4E, 0xF, 0xF, true));
+}
+__device__ __forceinline__ c128 quad_sum(c128 v) { return c128{quad_sum(v.re), quad_sum(v.im)}; }
 
 // Sum over a 256-thread group; every thread gets the total.
 __device__ __forceinline__ c128 group_sum(c128 v, c128* red) {
@@ -122,7 +153,10 @@ __global__ __launch_bounds__(64) void k_nl_comb(int n, int m, const c128* __rest
 // with the stored inverses of the 64 x 64 diagonal blocks.  Thread (wave w,
 // lane l) owns rows 16w..16w+15 of the block and column l of every column
 // block (coalesced row segments); its 16 partial sums are reduced over the
-// wave once, at the end.  A group takes its block from a ticket counter, so
+// wave once, before the last two blocks appear, which are applied four lanes a
+// row from registers: between their solutions and its own a block has 16
+// products and two exchanges, where the sums' reduction took 5 us (n = 2048:
+// 225 -> 173 us per triangle).  A group takes its block from a ticket counter, so
 // blocks are taken in launch order and a group only waits for blocks already
 // held by running groups; the waits are bounded (a wait that runs out sets
 // *err and the group finishes with wrong values instead of hanging).  Block
@@ -163,6 +197,7 @@ __global__ __launch_bounds__(512) void k_nl_tri(int n, int ld, const c128* __res
   __shared__ c128 Dsh[2][B][B + 1];
   __shared__ c128 tq[2][B];
   __shared__ c128 ysh[2][B];
+  __shared__ c128 yw[8][B];  // per wave: a block's solution
   __shared__ int s_t;
   const int nblk = (n + B - 1) / B, npair = (nblk + 1) / 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -195,103 +230,125 @@ __global__ __launch_bounds__(512) void k_nl_tri(int n, int ld, const c128* __res
   c128 acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = c128{0.0, 0.0};
-  // this wave's 16 right-hand-side entries, loaded now (they do not depend on
-  // the chain): lane i < 16 holds row 16 hw + i
+  // the right-hand-side entry of row 16 hw + lane/4, loaded now (it does not
+  // depend on the chain)
+  const int row = 16 * hw + (lane >> 2), k0 = (lane & 3) * 16;
   c128 rhs_mine = {0.0, 0.0};
-  if (lane < 16 && qmine >= 0) {
-    const int r = qmine * B + 16 * hw + lane;
-    if (r < n) rhs_mine = UPPER ? b[r] : b[rat[r]];
-  }
+  if (qmine >= 0 && qmine * B + row < n) rhs_mine = UPPER ? b[qmine * B + row] : b[rat[qmine * B + row]];
   // column blocks solved by other groups, in the order they appear
   const int c_first = UPPER ? nblk - 1 : 0;
   const int ncb = UPPER ? max(0, nblk - 1 - max(qf, qs)) : 2 * pr;
   auto cb = [&](int s) { return UPPER ? c_first - s : c_first + s; };
+  const int nl = min(2, ncb), nst = ncb - nl;  // the last two blocks are applied apart, below
   c128 seg[16];
   auto load_seg = [&](int c) {
     const int col = c * B + lane;
 #pragma unroll
     for (int i = 0; i < 16; ++i) seg[i] = (roff[i] >= 0 && col < n) ? T[roff[i] + col] : c128{0.0, 0.0};
   };
-  // waves 4-7 also need the segment of the first block (their coupling)
-  const int nseg = ncb + (half == 1 ? 1 : 0);
-  auto seg_col = [&](int s) { return s < ncb ? cb(s) : qf; };
-  if (nseg > 0) load_seg(seg_col(0));
+  if (nst > 0) load_seg(cb(0));
   // Blocks are published in the order cb(0), cb(1), ... (a group publishes
   // only after consuming every block before its own), so once the flag of
   // cb(ncb - 1) is seen, every block this group needs is there: one wait and
   // one acquire cover them all, and each block's solution can be loaded one
   // block ahead like the factor segments.
   int known = 0;  // blocks cb(0..known-1) are acquired
-  c128 ynext = {0.0, 0.0};
-  for (int s = 0; s < ncb; ++s) {
-    const int c = cb(s);
-    const int col = c * B + lane;
-    c128 yc;
-    if (s >= known) {
-      int kn = s + 1;
-      if (lane == 0) {
-        wait_flag(flags + c, epoch, err);
-        if (s + 1 < ncb &&
-            __hip_atomic_load(flags + cb(ncb - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch)
-          kn = ncb;
-      }
-      known = __shfl(kn, 0, 64);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      yc = col < n ? out[col] : c128{0.0, 0.0};
-    } else {
-      yc = ynext;
+  auto await = [&](int s) {
+    if (s < known) return;
+    int kn = s + 1;
+    if (lane == 0) {
+      wait_flag(flags + cb(s), epoch, err);
+      if (s + 1 < ncb && __hip_atomic_load(flags + cb(ncb - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch)
+        kn = ncb;
     }
-    if (s + 1 < known) {
+    known = __shfl(kn, 0, 64);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  };
+  c128 ynext = {0.0, 0.0};
+  int have = 0;  // ynext holds block have - 1
+  for (int s = 0; s < nst; ++s) {
+    const int col = cb(s) * B + lane;
+    await(s);
+    const c128 yc = have == s + 1 ? ynext : col < n ? out[col] : c128{0.0, 0.0};
+    if (s + 1 < known && s + 1 < nst) {
       const int ncol = cb(s + 1) * B + lane;
       ynext = ncol < n ? out[ncol] : c128{0.0, 0.0};
+      have = s + 2;
     }
     c128 cur[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) cur[i] = seg[i];
-    if (s + 1 < nseg) load_seg(seg_col(s + 1));  // the next segment loads during this one's use
+    if (s + 1 < nst) load_seg(cb(s + 1));  // the next segment loads during this one's use
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = acc[i] + cur[i] * yc;
   }
+  // The 16 rows' sums over the lanes, halving the rows with the lanes: lane l
+  // keeps row l/4, a quarter of its sum in each lane of the four.
+#pragma unroll
+  for (int o = 32, m = 8; m >= 1; o >>= 1, m >>= 1) {
+    const bool hi = lane & o;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i < m) {
+        const c128 keep = hi ? acc[i + m] : acc[i], send = hi ? acc[i] : acc[i + m];
+        acc[i] = c128{keep.re + __shfl_xor(send.re, o, 64), keep.im + __shfl_xor(send.im, o, 64)};
+      }
+  }
+  c128 sum = acc[0];
+  // The blocks on the critical path (the group before solves the last two, and
+  // this one its first for its second): 16 columns of a row per lane, in
+  // registers before the solution is there, so that only these products and
+  // two exchanges stand between it and t.
+  const long long rbase = qmine >= 0 && qmine * B + row < n ? (long long)rat[qmine * B + row] * ld : -1;
+  c128 near[3][16];
+  auto load_near = [&](c128 (&v)[16], int c) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = rbase >= 0 && c * B + k0 + k < n ? T[rbase + c * B + k0 + k] : c128{0.0, 0.0};
+  };
+  auto apply_near = [&](const c128 (&v)[16], const c128* y) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) sum = sum + v[k] * y[k0 + k];
+  };
+  if (nl > 1) load_near(near[0], cb(ncb - 2));
+  if (nl > 0) load_near(near[1], cb(ncb - 1));
+  if (half == 1 && qs >= 0) load_near(near[2], qf);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int s = ncb - 2 + u;
+    if (s < 0) continue;
+    await(s);
+    const int col = cb(s) * B + lane;
+    yw[w][lane] = col < n ? out[col] : c128{0.0, 0.0};
+    __builtin_amdgcn_wave_barrier();  // (a wave's LDS accesses stay in order)
+    apply_near(near[u], yw[w]);
+    __builtin_amdgcn_wave_barrier();
+  }
   // solve the group's blocks in order: t_q = b_q - row sums, y_q = Dinv_q t_q
-  auto publish_sums = [&](int h) {  // waves of half h
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = wave_sum(acc[i]);
-    if (lane < 16) {
-      c128 v = {0.0, 0.0};
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (i == lane) v = acc[i];
-      tq[h][16 * hw + lane] = rhs_mine - v;
-    }
+  auto put_t = [&](int h) {
+    const c128 v = quad_sum(sum);
+    if ((lane & 3) == 0) tq[h][row] = rhs_mine - v;
   };
   auto apply_inverse = [&](int h) {  // the 256 threads of half h: four per row
-    const int i = htid >> 2, k0 = (htid & 3) * 16;
     c128 y = {0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < 16; ++k) y = y + Dsh[h][i][k0 + k] * tq[h][k0 + k];
-    y.re += __shfl_xor(y.re, 1, 64);
-    y.im += __shfl_xor(y.im, 1, 64);
-    y.re += __shfl_xor(y.re, 2, 64);
-    y.im += __shfl_xor(y.im, 2, 64);
-    if ((htid & 3) == 0) ysh[h][i] = y;
+    for (int k = 0; k < 16; ++k) y = y + Dsh[h][row][k0 + k] * tq[h][k0 + k];
+    y = quad_sum(y);
+    if ((lane & 3) == 0) ysh[h][row] = y;
   };
   auto store_publish = [&](int h, int q) {  // one wave: its release orders its own stores before the flag
     if (q * B + lane < n) out[q * B + lane] = ysh[h][lane];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (lane == 0) __hip_atomic_store(flags + q, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (half == 0) publish_sums(0);
+  if (half == 0) put_t(0);
   __syncthreads();
   if (half == 0) apply_inverse(0);
   __syncthreads();
   if (w == 0) store_publish(0, qf);
-  if (qs < 0) return;  // wave-uniform: no second block
+  if (qs < 0) return;  // uniform over the group: no second block
   if (half == 1) {
-    // coupling to the first block: seg holds its segment
-    const c128 yc = ysh[0][lane];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = acc[i] + seg[i] * yc;
-    publish_sums(1);
+    apply_near(near[2], ysh[0]);  // coupling to the first block
+    put_t(1);
   }
   __syncthreads();
   if (half == 1) apply_inverse(1);
@@ -1407,10 +1464,7 @@ nep_status nep_nleigs(nep_split h, const nep_contour* g, const nep_nleigs_opts* 
     std::vector<int> keep;
     for (int a = 0; a < nc; ++a)
       if (eh[a] <= eta_tol) keep.push_back(a);
-    std::sort(keep.begin(), keep.end(), [&](int x, int y) {
-      const zc lx = lam[cand[x]], ly = lam[cand[y]];
-      return lx.real() != ly.real() ? lx.real() < ly.real() : lx.imag() < ly.imag();
-    });
+    order_pairs(keep, [&](int x) { return lam[cand[x]]; });
     mret = std::min((int)keep.size(), o->max_eigs);
     for (int a = 0; a < mret; ++a) {
       const int b = keep[a];
@@ -1761,10 +1815,7 @@ nep_status nep_nleigs_batch(int nprob, const nep_split* h, const nep_contour* g,
   std::vector<c128*> dst;
   for (int p = 0; p < P; ++p) {
     auto& kp = keep[p];
-    std::sort(kp.begin(), kp.end(), [&](int x, int y) {
-      const c128 lx = pairs[x].lam, ly = pairs[y].lam;
-      return lx.re != ly.re ? lx.re < ly.re : lx.im < ly.im;
-    });
+    order_pairs(kp, [&](int x) { return zc(pairs[x].lam.re, pairs[x].lam.im); });
     const int mr = std::min((int)kp.size(), maxe);
     m_out[p] = mr;
     for (int a = 0; a < mr; ++a) {
