@@ -232,9 +232,19 @@ struct LrJob {
   c128* Zp;         // S partial sums of Z (S x r x NL), used when S > 1
   int S, srows;     // the sum over s cut into S ranges of srows rows
 };
+// The terms in rounds whose partial sums fit their scratch together: jobs
+// first .. first + cnt - 1, with the prefix tables of their tiles and of their
+// 256-element groups of k_lr_zsum at off (cnt + 1 ints each).
+struct LrTables {
+  struct Round {
+    int first, cnt, off, tiles, sums;
+  };
+  const LrJob* jobs = nullptr;  // device
+  const int* prefix = nullptr;  // device
+  std::vector<Round> rounds;
+};
 hipError_t resid_run(const ProbDesc* pd, const int* prefix, const Table& t, const Table& tr, int resid_big, const NodeArrays& na,
-                     const c128* Y, c128* R, IrState ir, int nnodes, hipStream_t st, const LrJob* lr = nullptr,
-                     int nlr = 0);
+                     const c128* Y, c128* R, IrState ir, int nnodes, hipStream_t st, const LrTables& lr);
 // status read-back block (see k_gather_status) and its size
 size_t status_bytes(int G);
 // (pmin: smallest pivot moduli to start from, or nullptr: see min_pivot)

@@ -346,6 +346,48 @@ nep_status MomentsPlan::bordered_solve(bool refine, hipStream_t st) {
   return NEP_OK;
 }
 
+nep_status MomentsPlan::upload_lr_jobs(size_t scratch, hipStream_t st) {
+  lr_.rounds.clear();
+  lr_prefix_.clear();
+  if (lr_jobs_.empty()) return NEP_OK;
+  const int nj = (int)lr_jobs_.size();
+  std::vector<size_t> at(nj, 0);
+  auto partial = [](const LrJob& J) { return J.S > 1 ? (size_t)J.S * J.r * J.NL : (size_t)0; };
+  size_t need = 0;
+  for (int f = 0; f < nj;) {
+    LrTables::Round q{f, 0, (int)lr_prefix_.size(), 0, 0};
+    size_t used = 0;
+    std::vector<int> sums;
+    while (f + q.cnt < nj) {
+      const LrJob& J = lr_jobs_[f + q.cnt];
+      if (q.cnt > 0 && used + partial(J) > scratch) break;
+      at[f + q.cnt++] = used;
+      used += partial(J);
+      lr_prefix_.push_back(q.tiles);
+      sums.push_back(q.sums);
+      q.tiles += ceil_div(J.r, 64) * ceil_div(J.NL, 32) * J.S;
+      if (J.S > 1) q.sums += (int)ceil_div_ll((long long)J.r * J.NL, 256);
+    }
+    lr_prefix_.push_back(q.tiles);
+    lr_prefix_.insert(lr_prefix_.end(), sums.begin(), sums.end());
+    lr_prefix_.push_back(q.sums);
+    need = std::max(need, used);
+    lr_.rounds.push_back(q);
+    f += q.cnt;
+  }
+  if (dlrzp_.bytes < sizeof(c128) * need) NEP_TRY(dlrzp_.alloc(sizeof(c128) * need));
+  for (int f = 0; f < nj; ++f)
+    if (lr_jobs_[f].S > 1) lr_jobs_[f].Zp = dlrzp_.as<c128>() + at[f];
+  const size_t jb = sizeof(LrJob) * nj, pb = sizeof(int) * lr_prefix_.size();
+  if (dlr_jobs_.bytes < jb) NEP_TRY(dlr_jobs_.alloc(jb));
+  if (dlr_prefix_.bytes < pb) NEP_TRY(dlr_prefix_.alloc(pb));
+  NEP_HIP(hipMemcpyAsync(dlr_jobs_.p, lr_jobs_.data(), jb, hipMemcpyHostToDevice, st));
+  NEP_HIP(hipMemcpyAsync(dlr_prefix_.p, lr_prefix_.data(), pb, hipMemcpyHostToDevice, st));
+  lr_.jobs = dlr_jobs_.as<LrJob>();
+  lr_.prefix = dlr_prefix_.as<int>();
+  return NEP_OK;
+}
+
 nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, hipStream_t st) {
   // Z blocks of the low-rank terms of real problems (the complex-term
   // residual multiplies every term densely)
@@ -355,23 +397,15 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
       for (int i = 0; i < probs[p].op->ell; ++i) zelems += (size_t)probs[p].op->lr_rank[i] * opt.N * opt.L;
   if (zelems > 0 && dlrz_.bytes < sizeof(c128) * zelems) NEP_TRY(dlrz_.alloc(sizeof(c128) * zelems));
   // Z = H^T Y sums over the problem's n rows: cut into S ranges (at most 16,
-  // at least 256 rows each, a multiple of 32) so that enough groups run;
-  // the partial sums of one job at a time live in dlrzp_.
+  // at least 256 rows each, a multiple of 32) so that enough groups run.  All
+  // terms run in one launch while their partial sums fit kLrScratch elements
+  // of dlrzp_ (1 GiB), in rounds beyond.
+  constexpr size_t kLrScratch = (size_t)1 << 26;
   auto lr_split = [](int n, int& S, int& srows) {
     S = std::max(1, std::min(16, n / 256));
     srows = ((n + S - 1) / S + 31) / 32 * 32;
     S = (n + srows - 1) / srows;
   };
-  size_t pelems = 0;
-  for (int p = 0; p < nprob; ++p)
-    if (!probs[p].op->a_cplx)
-      for (int i = 0; i < probs[p].op->ell; ++i) {
-        int S, srows;
-        lr_split(probs[p].op->n, S, srows);
-        if (probs[p].op->lr_rank[i] > 0 && S > 1)
-          pelems = std::max(pelems, (size_t)S * probs[p].op->lr_rank[i] * opt.N * opt.L);
-      }
-  if (pelems > 0 && dlrzp_.bytes < sizeof(c128) * pelems) NEP_TRY(dlrzp_.alloc(sizeof(c128) * pelems));
   lr_jobs_.clear();
   size_t zoff = 0;
   for (int p = 0; p < nprob; ++p) {
@@ -385,8 +419,8 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
       if (rk > 0) {
         int S, srows;
         lr_split(D.n, S, srows);
-        lr_jobs_.push_back(LrJob{q.op->dLrH[i], dlrz_.as<c128>() + zoff, D.offY, D.n, rk, opt.N * opt.L,
-                                 S > 1 ? dlrzp_.as<c128>() : nullptr, S, srows});
+        lr_jobs_.push_back(LrJob{q.op->dLrH[i], dlrz_.as<c128>() + zoff, D.offY, D.n, rk, opt.N * opt.L, nullptr, S,
+                                 srows});
         zoff += (size_t)rk * opt.N * opt.L;
       }
     }
@@ -416,6 +450,7 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
     D.s_stride = q.s_stride > 0 ? q.s_stride : (long long)D.n * D.L;
     D.active = 1;
   }
+  NEP_TRY(upload_lr_jobs(kLrScratch, st));
   NEP_HIP(hipMemcpyAsync(dpd_.p, hpd_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
   return NEP_OK;
 }
@@ -769,8 +804,7 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
     // trip; nodes already converged skip the solve, which makes it a no-op
     // when the count turns out to be zero.
     for (int s = 0; s <= opt.max_refine; ++s) {
-      NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, Y, R, ir_, nnodes, st,
-                        lr_jobs_.data(), (int)lr_jobs_.size()));
+      NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, Y, R, ir_, nnodes, st, lr_));
       if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, Y, R, ir_, st));
       NEP_HIP(ir_control(pd, na_, ir_, nnodes, s, opt.tol, st));
       sweeps_run_ = s;
@@ -884,7 +918,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
                                st));
   for (int s = 0;; ++s) {
     NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, dY_.as<c128>(), dR_.as<c128>(), ir_, nnodes, st,
-                      lr_jobs_.data(), (int)lr_jobs_.size()));
+                      lr_));
     if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, dY_.as<c128>(), dR_.as<c128>(), ir_, st));
     NEP_HIP(ir_control(pd, na_, ir_, nnodes, opt.max_refine + 1 + s, opt.tol, st));
     if (s == kFallbackSweeps) break;

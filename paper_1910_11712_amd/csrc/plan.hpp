@@ -222,6 +222,7 @@ class MomentsPlan {
   int nprob = 0, nnodes = 0, Lmax = 0;
 
  private:
+  nep_status upload_lr_jobs(size_t scratch, hipStream_t st);
   nep_status upload_problems(const std::vector<PlanProblem>& probs, hipStream_t st);
   template <typename P>
   nep_status enqueue_t(hipStream_t st, bool eager, bool refactor);
@@ -237,7 +238,10 @@ class MomentsPlan {
   std::vector<ProbDesc> hpd_;
   std::vector<LrJob> lr_jobs_;  // low-rank terms of real problems (Z = H^T Y per residual)
   DevMem dlrz_;                 // their Z blocks
-  DevMem dlrzp_;                // partial sums of one Z block (the jobs run in turn on one stream)
+  DevMem dlrzp_;                // partial sums of a round's Z blocks (the rounds run in turn on one stream)
+  DevMem dlr_jobs_, dlr_prefix_;
+  std::vector<int> lr_prefix_;
+  LrTables lr_;
   std::vector<MatDesc> sorted_;  // the matrices with dense factors, largest first
   std::vector<MatDesc> shapes_;  // every matrix, largest first (identifies and tunes the plan)
   std::vector<int> prob_of_sorted_;

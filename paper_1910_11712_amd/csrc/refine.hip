@@ -335,15 +335,23 @@ __global__ __launch_bounds__(64 * WR * WQ, 4) void k_resid_real(const ProbDesc* 
 // partial sum to slice sp of Zp (Z itself when S == 1); k_lr_zsum then adds
 // the S slices in order, so the result does not depend on scheduling.  The
 // row tiles of one column tile and range read the same Y rows and are
-// consecutive virtual ids: they run on one XCD and share its L2.
-__global__ __launch_bounds__(256) void k_lr_z(const double* __restrict__ H, const c128* __restrict__ Y,
-                                              c128* __restrict__ Zp, int n, int r, int NL, int S, int srows,
-                                              int total) {
+// consecutive virtual ids: they run on one XCD and share its L2.  One launch
+// for every term of every problem: a term alone has 16 to 200 groups and takes
+// 60 us or more whatever its size (24 operators with eight such terms, six
+// sweeps: 11.3 ms one after the other, 8.5 together).
+__global__ __launch_bounds__(256) void k_lr_z(const LrJob* __restrict__ jobs, const int* __restrict__ prefix, int cnt,
+                                              const c128* __restrict__ Yb, int total) {
   constexpr int KC = 32;
   __shared__ __align__(16) double Hs[KC][66];
   __shared__ c128 Ys[KC][33];
-  const int v = xcd_remap(blockIdx.x, gridDim.x, total);
+  int v = xcd_remap(blockIdx.x, gridDim.x, total);
   if (v < 0) return;
+  const int slot = find_slot(prefix, cnt, v);
+  const LrJob& J = jobs[slot];
+  v -= prefix[slot];
+  const double* __restrict__ H = J.H;
+  const c128* __restrict__ Y = Yb + J.offY;
+  const int n = J.n, r = J.r, NL = J.NL, S = J.S, srows = J.srows;
   const int rb = (r + 63) / 64;
   const int pair = v / rb, sp = pair % S;
   const int k0 = (v % rb) * 64, c0 = (pair / S) * 32;
@@ -380,7 +388,7 @@ __global__ __launch_bounds__(256) void k_lr_z(const double* __restrict__ H, cons
     }
     __syncthreads();
   }
-  c128* out = Zp + (long long)sp * r * NL;
+  c128* __restrict__ out = (S > 1 ? J.Zp : J.Z) + (long long)sp * r * NL;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int k = k0 + 4 * tk + i;
@@ -390,18 +398,22 @@ __global__ __launch_bounds__(256) void k_lr_z(const double* __restrict__ H, cons
   }
 }
 
-// Z[i] = sum over sp = 0..S-1 of Zp[sp m + i], in that order.
-__global__ __launch_bounds__(256) void k_lr_zsum(const c128* __restrict__ Zp, c128* __restrict__ Z, int S,
-                                                 long long m) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+// Z[i] = sum over sp = 0..S-1 of Zp[sp m + i], in that order (terms of one
+// range have no groups here).
+__global__ __launch_bounds__(256) void k_lr_zsum(const LrJob* __restrict__ jobs, const int* __restrict__ prefix,
+                                                 int cnt) {
+  const int slot = find_slot(prefix, cnt, blockIdx.x);
+  const LrJob& J = jobs[slot];
+  const long long m = (long long)J.r * J.NL, i = (long long)(blockIdx.x - prefix[slot]) * 256 + threadIdx.x;
   if (i >= m) return;
+  const c128* __restrict__ Zp = J.Zp;
   c128 a = Zp[i];
-  for (int sp = 1; sp < S; ++sp) {
+  for (int sp = 1; sp < J.S; ++sp) {
     const c128 b = Zp[(long long)sp * m + i];
     a.re += b.re;
     a.im += b.im;
   }
-  Z[i] = a;
+  J.Z[i] = a;
 }
 
 // t: tiles of the complex-term kernel (64 x 64); tr: tiles of the real-term
@@ -411,17 +423,15 @@ __global__ __launch_bounds__(256) void k_lr_zsum(const c128* __restrict__ Zp, c1
 // order, k ascending in steps of 4), so the choice does not change results.
 hipError_t resid_run(const ProbDesc* pd, const int* prefix, const Table& t, const Table& tr, int resid_big,
                      const NodeArrays& na, const c128* Y, c128* R, IrState ir, int /*nnodes*/, hipStream_t st,
-                     const LrJob* lr, int nlr) {
-  for (int j = 0; j < nlr; ++j) {  // Z = H^T Y of every low-rank term, before the products that use it
-    const LrJob& J = lr[j];
-    const int total = ((J.r + 63) / 64) * ((J.NL + 31) / 32) * J.S;
-    hipLaunchKernelGGL(k_lr_z, dim3(xcd_grid(total)), dim3(256), 0, st, J.H, Y + J.offY, J.S > 1 ? J.Zp : J.Z, J.n,
-                       J.r, J.NL, J.S, J.srows, total);
+                     const LrTables& lr) {
+  for (const LrTables::Round& q : lr.rounds) {  // Z = H^T Y of every low-rank term, before the products that use it
+    hipLaunchKernelGGL(k_lr_z, dim3(xcd_grid(q.tiles)), dim3(256), 0, st, lr.jobs + q.first, lr.prefix + q.off, q.cnt, Y,
+                       q.tiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (J.S > 1) {
-      const long long m = (long long)J.r * J.NL;
-      hipLaunchKernelGGL(k_lr_zsum, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, J.Zp, J.Z, J.S, m);
+    if (q.sums > 0) {
+      hipLaunchKernelGGL(k_lr_zsum, dim3(q.sums), dim3(256), 0, st, lr.jobs + q.first, lr.prefix + q.off + q.cnt + 1,
+                         q.cnt);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
