@@ -179,7 +179,9 @@ typedef struct {
                              the factorizations (events; single calls and eager
                              batch runs; 0 for graph replays)                    */
   double min_abs_pivot;   /* smallest |u_kk| over the node factorizations in the
-                             path's precision (complex FP32 for the mixed path);
+                             path's precision (complex FP32 for the mixed path),
+                             of the band or of the chunks and the border where
+                             the terms are factored that way;
                              0 with NEP_ERR_SINGULAR, NaN if a factor holds NaN  */
 } nep_ciss_stats;
 
