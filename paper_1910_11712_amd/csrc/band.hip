@@ -11,9 +11,9 @@
 // consecutive entries: the factor is stored [row][entry][node], the right-hand
 // sides [row][node][column].  A lane's next rows are loaded into a second
 // register buffer while the current ones are eliminated.  Measured against the
-// dense path: 256 strings of 64..1024 rows (32 nodes, 8 probes) 187 -> 6.6 ms
-// per batch, one string of 200 rows with its extraction 1.44 -> 0.91 ms, of 65
-// rows 0.93 -> 0.69 ms; there is no size at which the dense path is faster.
+// dense path: 256 strings of 64..1024 rows (32 nodes, 8 probes) 187 -> 5.7 ms
+// per batch, one string of 200 rows with its extraction 1.44 -> 0.74 ms, of 65
+// rows 0.93 -> 0.53 ms; there is no size at which the dense path is faster.
 //
 // Storage of a problem (element offset offF), NE = 3W + 2 entries per row:
 //   0 .. 2W       first T(row, row - W .. row + W), then U(row, row .. row + 2W)
@@ -202,16 +202,19 @@ __global__ __launch_bounds__(64, 1) void k_band_lu(const ProbDesc* __restrict__ 
 // ---------------------------------------------------------------------------
 // Solve: one lane per (node, probe column).  kBandV: right-hand side V, Y = x;
 // kBandR: right-hand side R, Y = x; kBandRefine: right-hand side R, Y += x.
-// The forward sweep leaves its result where the backward sweep reads it: in Y,
-// which then takes the solution, or, where Y's old value is needed, over R
-// (which the next residual recomputes).
+// The forward sweep leaves its result where the backward sweep reads it.  With
+// FP32 factors that is Wb, in FP32 as it was computed: the solve is bound by
+// memory, and through R or Y it was widened to 16 bytes and back (256 strings of
+// 64..1024 rows, 32 nodes, 8 probes: 542 -> 484 us a sweep).  With FP64
+// factors it is Y, which then takes the solution, or, where Y's old value is
+// needed, R (which the next residual recomputes).
 // ---------------------------------------------------------------------------
 template <typename P, int W>
 __global__ __launch_bounds__(64, 1) void k_band_solve(const ProbDesc* __restrict__ pd, const int* __restrict__ prefix,
                                                       int cnt, const cx<P>* __restrict__ Fb,
                                                       const unsigned char* __restrict__ Pb, c128* __restrict__ Rb,
-                                                      c128* __restrict__ Yb, int mode, const int* __restrict__ conv,
-                                                      IrState ir) {
+                                                      c128* __restrict__ Yb, cx<P>* __restrict__ Wb, int mode,
+                                                      const int* __restrict__ conv, IrState ir) {
   const int v = blockIdx.x;
   const int p = find_slot(prefix, cnt, v);
   const ProbDesc& D = pd[p];
@@ -226,7 +229,9 @@ __global__ __launch_bounds__(64, 1) void k_band_solve(const ProbDesc* __restrict
   const long long rs = (long long)NE * N;
   const bool refine = mode == kBandRefine;
   c128* Y = Yb + D.offY + e;
-  c128* W0 = refine ? Rb + D.offY + e : Y;  // the forward sweep's result
+  cx<P>* W0;  // the forward sweep's result
+  if constexpr (sizeof(P) == 4) W0 = Wb + D.offBW + e;
+  else W0 = refine ? Rb + D.offY + e : Y;
   const c128* V = mode == kBandV ? D.V + (long long)c * n : Rb + D.offY + e;
   const long long vs = mode == kBandV ? 1 : NL;
 
@@ -262,7 +267,7 @@ __global__ __launch_bounds__(64, 1) void k_band_solve(const ProbDesc* __restrict
             t[i] = csel(b.q[u] == i, t[0], x);
             top = csel(b.q[u] == i, x, top);
           }
-          W0[(long long)r * NL] = c128{double(top.re), double(top.im)};
+          W0[(long long)r * NL] = top;
 #pragma unroll
           for (int i = 1; i <= W; ++i) t[i - 1] = fms(t[i], b.l[u][i - 1], top);
           t[W] = csel(r + W + 1 < n, cvt<P>(b.b[u]), cx<P>{P(0), P(0)});
@@ -285,7 +290,8 @@ __global__ __launch_bounds__(64, 1) void k_band_solve(const ProbDesc* __restrict
   constexpr int UB = U > 1 ? U / 2 : 1;
   struct Buf {
     cx<P> u[UB][2 * W], inv[UB];
-    c128 y[UB], o[UB];
+    cx<P> y[UB];
+    c128 o[UB];
   };
   Buf b0, b1;
   auto load = [&](Buf& b, int r0) {  // rows r0, r0 - 1, ..
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(64, 1) void k_band_solve(const ProbDesc* __restrict
     for (int u = 0; u < UB; ++u) {
       const int r = r0 - u;
       if (r >= 0) {
-        cx<P> s = cvt<P>(b.y[u]);
+        cx<P> s = b.y[u];
         // the nearest unknown last: the others do not wait for it
 #pragma unroll
         for (int i = 2 * W - 1; i >= 0; --i) s = fms(s, b.u[u][i], x[i]);
@@ -485,12 +491,12 @@ hipError_t band_factor(const BandTables& bt, const ProbDesc* pd, const int* pref
 
 template <typename P>
 hipError_t band_solve(const BandTables& bt, const ProbDesc* pd, const int* prefix, const cx<P>* F,
-                      const unsigned char* piv, c128* R, c128* Y, int mode, const int* conv, IrState ir,
+                      const unsigned char* piv, c128* R, c128* Y, cx<P>* Wf, int mode, const int* conv, IrState ir,
                       hipStream_t st) {
 #define NEP_BAND_SOLVE(k, W)                                                                                      \
   if (bt.solve[k].total > 0)                                                                                      \
   hipLaunchKernelGGL((k_band_solve<P, W>), dim3(bt.solve[k].total), dim3(64), 0, st, pd, prefix + bt.solve[k].off, \
-                     bt.solve[k].cnt, F, piv, R, Y, mode, conv, ir)
+                     bt.solve[k].cnt, F, piv, R, Y, Wf, mode, conv, ir)
   NEP_BAND_CLASSES(NEP_BAND_SOLVE);
 #undef NEP_BAND_SOLVE
   return hipGetLastError();
@@ -523,7 +529,7 @@ hipError_t band_logdet(const BandTables& bt, const ProbDesc* pd, const int* pref
   template hipError_t band_factor<P>(const BandTables&, const ProbDesc*, const int*, const NodeArrays&, cx<P>*,      \
                                      unsigned char*, int*, double*, const int*, hipStream_t);                        \
   template hipError_t band_solve<P>(const BandTables&, const ProbDesc*, const int*, const cx<P>*,                    \
-                                    const unsigned char*, c128*, c128*, int, const int*, IrState, hipStream_t);      \
+                                    const unsigned char*, c128*, c128*, cx<P>*, int, const int*, IrState, hipStream_t); \
   template hipError_t band_logdet<P>(const BandTables&, const ProbDesc*, const int*, const cx<P>*,                   \
                                      const unsigned char*, int, double*, hipStream_t);
 NEP_BAND_INST(float)

@@ -67,6 +67,7 @@ struct ProbDesc {
   int bordered;           // 1: takes the bordered path, with
   const float *G32, *H32; // the low-rank factors side by side (rows and columns padded to blocks)
   long long offF, offP;   // its factor (elements) and pivot bytes
+  long long offBW;        // band path: its forward results (elements)
   const c128* fpts;       // with zpts: given coefficients in place of f_i(z_j), at
                           // fpts[j*ell + i] (device), or nullptr
 };
@@ -153,11 +154,12 @@ void band_tables(BandTables& bt, std::vector<int>& buf, const std::vector<ProbDe
 template <typename P>
 hipError_t band_factor(const BandTables& bt, const ProbDesc* pd, const int* prefix, const NodeArrays& na, cx<P>* F,
                        unsigned char* piv, int* info, double* pmin, const int* skip, hipStream_t st);
-// kBandV: Y = T^{-1} V; kBandR: Y = T^{-1} R; kBandRefine: Y += T^{-1} R, R overwritten
+// kBandV: Y = T^{-1} V; kBandR: Y = T^{-1} R; kBandRefine: Y += T^{-1} R.  Wf: n x N*L entries per problem at offBW
+// for FP32 factors (FP64 ones leave the forward sweep's result in Y, or in R for kBandRefine)
 enum { kBandV = 0, kBandR = 1, kBandRefine = 2 };
 template <typename P>
 hipError_t band_solve(const BandTables& bt, const ProbDesc* pd, const int* prefix, const cx<P>* F,
-                      const unsigned char* piv, c128* R, c128* Y, int mode, const int* conv, IrState ir,
+                      const unsigned char* piv, c128* R, c128* Y, cx<P>* Wf, int mode, const int* conv, IrState ir,
                       hipStream_t st);
 hipError_t band_resid(const BandTables& bt, const ProbDesc* pd, const int* prefix, const NodeArrays& na,
                       const c128* Y, c128* R, IrState ir, hipStream_t st);

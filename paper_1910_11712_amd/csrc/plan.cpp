@@ -500,7 +500,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   std::vector<int> hprob, hj;
   std::vector<MatDesc> all;
   std::vector<MatDesc> dense;
-  long long offT = 0, offW = 0, offY = 0, offF = 0, offP = 0;
+  long long offT = 0, offW = 0, offY = 0, offF = 0, offP = 0, offBW = 0;
   int offRow = 0, g = 0;
   for (int p = 0; p < nprob; ++p) {
     const int n = probs[p].op->n;
@@ -519,6 +519,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     D.band = o.dense ? 0 : band_of(*probs[p].op);
     D.offF = offF;
     D.offP = offP;
+    D.offBW = offBW;
     {
       // the refinement, and the dense FP64 re-solve behind it, have to be there
       int rank, nch;
@@ -540,6 +541,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     if (D.band) {
       offF += (long long)o.N * n * band_entries(D.band);
       offP += (long long)o.N * n;
+      offBW += (long long)o.N * n * o.L;
     } else if (!D.bordered) {
       offT += (long long)o.N * D.strideT;
     }
@@ -621,6 +623,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_TRY(A(dlu_prefix_, sizeof(int) * std::max<size_t>(1, lu_.prefix.size())));
   NEP_TRY(A(dT_, es * (size_t)t_elems_));
   NEP_TRY(A(dF_, es * (size_t)f_elems_));
+  NEP_TRY(A(dbw_, o.prec == NEP_PREC_FP64 ? 0 : sizeof(c64) * (size_t)offBW));
   NEP_TRY(A(dpiv_, (size_t)offP));
   NEP_TRY(A(dpmin_, any_band_ || !bp_.empty() ? sizeof(double) * (size_t)nnodes : 0));
   NEP_TRY(A(dmd64_, bp_.empty() ? 0 : sizeof(MatDesc) * sorted64_.size()));
@@ -786,7 +789,7 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
       NEP_HIP(hipStreamWaitEvent(sx, ev_beside_[0], 0));
     }
     if (any_band_)
-      NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, refine ? kBandRefine : kBandV, ir_.conv, ir_,
+      NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, dbw_.as<cx<P>>(), refine ? kBandRefine : kBandV, ir_.conv, ir_,
                             sx));
     if (!bp_.empty()) NEP_TRY(bordered_solve(refine, sx));
     NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, refine ? R : nullptr, Y, refine, ir_.conv, ir_, st));
@@ -914,7 +917,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
                             skip, ir_, st));
   if (any_band_)
-    NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandV, skip, ir_,
+    NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), nullptr, kBandV, skip, ir_,
                                st));
   for (int s = 0;; ++s) {
     NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, dY_.as<c128>(), dR_.as<c128>(), ir_, nnodes, st,
@@ -928,7 +931,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
                               true, ir_.conv, ir_, st));
     if (any_band_)
-      NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), kBandRefine, ir_.conv,
+      NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), nullptr, kBandRefine, ir_.conv,
                                  ir_, st));
   }
   fallback_pending_ = true;
@@ -955,7 +958,7 @@ nep_status MomentsPlan::solve_rhs_t(hipStream_t st) {
                        nullptr, ir_, st));
   if (any_band_)
     NEP_HIP(band_solve<P>(bt_, dpd_.as<ProbDesc>(), dprefix_.as<int>(), dF_.as<cx<P>>(), dpiv_.as<unsigned char>(),
-                          dR_.as<c128>(), dY_.as<c128>(), kBandR, nullptr, ir_, st));
+                          dR_.as<c128>(), dY_.as<c128>(), dbw_.as<cx<P>>(), kBandR, nullptr, ir_, st));
   return NEP_OK;
 }
 
