@@ -3,12 +3,14 @@
 // refinement residual R.
 //
 // The LU writes, as its panels complete, the inverses of the 64 x 64 diagonal
-// blocks of L (unit lower) and U.  k_trsv runs one launch per solve: a group
-// owns one node and a group of Lg right-hand columns and runs forward then
-// backward substitution over 64-row blocks (right-looking, accumulators in
-// registers; see the kernel).  The right-hand side is gathered through the
-// row map; the result is stored to (or, for a correction, added to) Y in
-// FP64, with the column maxima of |Y| for the refinement test.
+// blocks of L (unit lower) and U.  One launch per solve and size class: a
+// group owns one node and a group of right-hand columns and runs forward then
+// backward substitution over 64-row blocks, right-looking, with the right-hand
+// sides of all rows in registers: k_trsm on the matrix cores (8 columns), or
+// k_trsv on the vector units (4, 8 or 16), which is left for complex-FP64
+// factors of more than 1024 rows and for the tuner.  The right-hand side is
+// gathered through the row map; the result is stored to (or, for a correction,
+// added to) Y in FP64, with the column maxima of |Y| for the refinement test.
 #include "engine.hpp"
 
 namespace nep {
