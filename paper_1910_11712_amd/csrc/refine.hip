@@ -507,7 +507,9 @@ __global__ __launch_bounds__(64 * kIrControlWaves) void k_ir_control(const ProbD
     if (!ir.conv[g] && ir_control_node(pd, na, ir, g, sweep, tol)) ++mine;
   if (mine > 0) atomicAdd(&unconv, mine);
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && gridDim.x == 1) {
+    ir.counters[0] = unconv;
+  } else if (threadIdx.x == 0) {
     const unsigned add = (1u << kIrCountBits) | (unsigned)unconv;
     const unsigned sum = atomicAdd(reinterpret_cast<unsigned*>(ir.counters) + 2, add) + add;
     if (sum >> kIrCountBits == gridDim.x) {
@@ -539,8 +541,9 @@ __global__ void k_ir_reset(IrState ir, int nnodes) {
 
 hipError_t ir_control(const ProbDesc* pd, const NodeArrays& na, IrState ir, int nnodes, int sweep, double tol,
                       hipStream_t st) {
-  if (nnodes >= 1 << kIrCountBits) return hipErrorInvalidValue;
-  const int groups = std::max(1, std::min(kIrControlGroups, ceil_div(nnodes, kIrControlWaves)));
+  // (more nodes than the packed word counts: one group)
+  const int groups =
+      nnodes >= 1 << kIrCountBits ? 1 : std::max(1, std::min(kIrControlGroups, ceil_div(nnodes, kIrControlWaves)));
   hipLaunchKernelGGL(k_ir_control, dim3(groups), dim3(64 * kIrControlWaves), 0, st, pd, na, ir, nnodes, sweep, tol);
   return hipGetLastError();
 }
