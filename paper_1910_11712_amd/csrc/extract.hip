@@ -482,53 +482,66 @@ __global__ __launch_bounds__(256) void k_wy_gram(const c128* __restrict__ B, lon
   }
 }
 
-// X = T V_1^H U (r x m), V_1 the top r rows of V: one group per column
-__global__ __launch_bounds__(256) void k_wy_coef(const c128* __restrict__ B, long long M, int r,
-                                                 const c128* __restrict__ tau, const c128* __restrict__ G,
-                                                 const c128* __restrict__ U, c128* __restrict__ X) {
+// X = T V_1^H U (r x m), V_1 the top r rows of V: one group per column, 256
+// rows of the back substitution at a time, a row per thread (blocks of K*L <=
+// 256 columns are one such block; probe pools reach 4096).
+constexpr int kWyRows = 256;
+
+__global__ __launch_bounds__(kWyRows) void k_wy_coef(const c128* __restrict__ B, long long M, int r,
+                                                     const c128* __restrict__ tau, const c128* __restrict__ G,
+                                                     const c128* __restrict__ U, c128* __restrict__ X) {
   __shared__ c128 xk;
-  const int i = threadIdx.x, j = blockIdx.x;
-  c128 c = {0.0, 0.0};
-  if (i < r) {
-    c = U[(long long)j * r + i];
-    for (int l = i + 1; l < r; ++l) c = cmac(c, conj(B[(long long)i * M + l]), U[(long long)j * r + l]);
-  }
-  for (int k = r - 1; k >= 0; --k) {
-    if (i == k) {
-      xk = tau[k] * c;
-      X[(long long)j * r + k] = xk;
+  const int j = blockIdx.x;
+  for (int b0 = (r - 1) / kWyRows * kWyRows; b0 >= 0; b0 -= kWyRows) {
+    const int i = b0 + threadIdx.x, top = min(r, b0 + kWyRows);
+    c128 c = {0.0, 0.0};
+    if (i < top) {
+      c = U[(long long)j * r + i];
+      for (int l = i + 1; l < r; ++l) c = cmac(c, conj(B[(long long)i * M + l]), U[(long long)j * r + l]);
+      for (int k = r - 1; k >= top; --k) c = fms(c, G[(long long)k * r + i], X[(long long)j * r + k]);
     }
-    __syncthreads();
-    if (i < k) c = fms(c, G[(long long)k * r + i], xk);
-    __syncthreads();
+    for (int k = top - 1; k >= b0; --k) {
+      if (i == k) {
+        xk = tau[k] * c;
+        X[(long long)j * r + k] = xk;
+      }
+      __syncthreads();
+      if (i < k) c = fms(c, G[(long long)k * r + i], xk);
+      __syncthreads();  // (also makes the block's X visible to the next one)
+    }
   }
 }
 
-// V0 = [U; 0] - V X: a thread per row, 8 columns per group
+// V0 = [U; 0] - V X: a thread per row, 8 columns per group, X staged kWyRows
+// rows at a time.
 __global__ __launch_bounds__(256) void k_wy_apply(const c128* __restrict__ B, long long M, int r, int m,
                                                   const c128* __restrict__ U, const c128* __restrict__ X,
                                                   c128* __restrict__ V0) {
   constexpr int CB = 8;
-  __shared__ c128 Xs[256][CB];
+  __shared__ c128 Xs[kWyRows][CB];
   const int j0 = blockIdx.y * CB;
-  for (int e = threadIdx.x; e < r * CB; e += 256) {
-    const int k = e / CB, j = e & (CB - 1);
-    Xs[k][j] = j0 + j < m ? X[(long long)(j0 + j) * r + k] : c128{0.0, 0.0};
-  }
-  __syncthreads();
   const long long row = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (row >= M) return;
   c128 acc[CB];
 #pragma unroll
   for (int j = 0; j < CB; ++j)
     acc[j] = (row < r && j0 + j < m) ? U[(long long)(j0 + j) * r + row] : c128{0.0, 0.0};
-  const int ke = (int)min((long long)r - 1, row);
+  for (int k0 = 0; k0 < r; k0 += kWyRows) {
+    const int kn = min(kWyRows, r - k0);
+    if (k0 > 0) __syncthreads();  // the staged rows are read
+    for (int e = threadIdx.x; e < kn * CB; e += 256) {
+      const int k = e / CB, j = e & (CB - 1);
+      Xs[k][j] = j0 + j < m ? X[(long long)(j0 + j) * r + k0 + k] : c128{0.0, 0.0};
+    }
+    __syncthreads();
+    const int ke = row < M ? (int)min((long long)kn, row - k0 + 1) : 0;
 #pragma unroll 4
-  for (int k = 0; k <= ke; ++k) {
-    const c128 v = row == k ? c128{1.0, 0.0} : B[(long long)k * M + row];
+    for (int k = 0; k < ke; ++k) {
+      const c128 v = row == k0 + k ? c128{1.0, 0.0} : B[(long long)(k0 + k) * M + row];
 #pragma unroll
-    for (int j = 0; j < CB; ++j) acc[j] = fms(acc[j], v, Xs[k][j]);
+      for (int j = 0; j < CB; ++j) acc[j] = fms(acc[j], v, Xs[k][j]);
+    }
   }
+  if (row >= M) return;
 #pragma unroll
   for (int j = 0; j < CB; ++j)
     if (j0 + j < m) V0[(long long)(j0 + j) * M + row] = acc[j];
@@ -940,8 +953,9 @@ nep_status extract_strided(Split& h, const nep_contour* g, const nep_ciss_opts* 
   {
     const int nt = ceil_div(KL, 4);
     hipLaunchKernelGGL(k_wy_gram, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, B0, M, KL, w.G.as<c128>());
-    hipLaunchKernelGGL(k_wy_coef, dim3(m), dim3(ceil_div(KL, 64) * 64), 0, st, B0, M, KL, tau, w.G.as<c128>(), Ur,
-                       w.wy.as<c128>());
+    hipLaunchKernelGGL(k_wy_coef, dim3(m), dim3(std::min(kWyRows, ceil_div(KL, 64) * 64)), 0, st, B0, M, KL, tau,
+                       w.G.as<c128>(), Ur, w.wy.as<c128>());
+    NEP_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_wy_apply, dim3((unsigned)ceil_div_ll(M, 256), ceil_div(m, 8)), dim3(256), 0, st, B0, M, KL, m,
                        Ur, w.wy.as<c128>(), V0);
     NEP_HIP(hipGetLastError());
