@@ -433,8 +433,10 @@ __global__ __launch_bounds__(kJacobiThreads) void k_jacobi(const c128* __restric
   __syncthreads();
   for (int j = pair; j < k; j += kJacobiMax / 2) {
     const double s = sv[j];
-    int pos = 0;  // descending, ties in column order
-    for (int i = 0; i < k; ++i) pos += (sv[i] > s || (sv[i] == s && i < j)) ? 1 : 0;
+    // descending, ties in column order; by their bits, so that a NaN (first) leaves a permutation too
+    auto key = [](double x) { return (unsigned long long)__double_as_longlong(x) & ~(1ull << 63); };
+    int pos = 0;
+    for (int i = 0; i < k; ++i) pos += (key(sv[i]) > key(s) || (key(sv[i]) == key(s) && i < j)) ? 1 : 0;
     if (l == 0) sout[pos] = ldexp(s, ex);
     for (int i = l; i < k; i += kJacobiLanes) {
       Wout[(long long)pos * k + i] = s > 0.0 ? c128{A[j][i].re / s, A[j][i].im / s} : c128{0.0, 0.0};

@@ -110,3 +110,23 @@ def test_probe_augmentation_past_256_columns(nep):
     for x in inside:
         assert np.min(np.abs(r["lam"] - x)) <= bound
     op.close()
+
+
+def test_moments_that_hold_nan(nep):
+    """Refused as moments without a rank, and no singular value is left over from the call before."""
+    n, L, K, N = 40, 4, 4, 64
+    con = Contour.circle(0.0, 1.0)
+    p, d, V, S = _diag_moments(n, L, K, [0.3 + 0.1j], con, N)
+    op = nep.SplitOperator.from_problem(p)
+    B = nep.binding
+    X = torch.zeros((K * L, n), dtype=torch.complex128, device="cuda")
+    Sd = torch.from_numpy(np.ascontiguousarray(S.transpose(0, 2, 1))).to("cuda")
+    opts = B.opts_struct(N, L, K, "mixed")
+    good = B.nep_extract(op.h, con, opts, Sd, X, max_eigs=K * L)
+    assert np.all(np.isfinite(good["sigma"]))
+    Sd[1, 2, 7] = float("nan")
+    with pytest.raises(B.NepError) as e:
+        B.nep_extract(op.h, con, opts, Sd, X, max_eigs=K * L)
+    assert e.value.m == 0
+    assert np.all(np.isnan(e.value.sigma)), e.value.sigma
+    op.close()
