@@ -18,10 +18,8 @@ namespace nep {
 static nep_status count_from_plan(MomentsPlan& plan, int n, hipStream_t st, int* count, double* max_step,
                                   double* winding) {
   const int G = plan.nnodes;
-  std::vector<int> info(G), bad(G);
-  NEP_HIP(hipMemcpyAsync(info.data(), plan.info(), sizeof(int) * G, hipMemcpyDeviceToHost, st));
-  NEP_HIP(hipMemcpyAsync(bad.data(), plan.nodes().bad, sizeof(int) * G, hipMemcpyDeviceToHost, st));
-  NEP_HIP(hipStreamSynchronize(st));
+  std::vector<int> info, bad;
+  NEP_TRY(plan.node_flags(st, info, bad));
   for (int g = 0; g < G; ++g) {
     NEP_CHECK(!bad[g], NEP_ERR_NOT_HOLOMORPHIC, "node %d lies on a pole or branch cut of some f_i", g);
     NEP_CHECK(info[g] >= n, NEP_ERR_SINGULAR, "node %d: exact zero pivot", g);

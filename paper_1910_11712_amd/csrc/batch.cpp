@@ -75,8 +75,8 @@ nep_status nep_batch_run(nep_batch b, nep_ciss_stats* st) {
   NEP_CHECK(b != nullptr, NEP_ERR_ARG, "null batch");
   Batch& B = b->impl;
   if (B.use_graph) {
-    NEP_HIP(hipGraphLaunch(B.exec, B.stream));
-    B.plan->replayed();
+    if (!B.plan->all_dense()) NEP_HIP(hipGraphLaunch(B.exec, B.stream));
+    NEP_TRY(B.plan->replayed(B.stream));
   } else {
     NEP_TRY(B.plan->enqueue(B.stream, false));
   }

@@ -18,8 +18,9 @@
 // Pivots are sought inside a chunk's window and inside the border only, so
 // unlike the dense LU's the factors are not backward stable for every T: the
 // FP64 refinement decides.  Its residual is that of T itself, and a node that
-// it cannot bring to the tolerance (a chunk near singular where T is not) is
-// solved by the dense FP64 factorization, as any other node would be.
+// it cannot bring to the tolerance (a chunk near singular where T is not)
+// hands its problem over to dense factors (MomentsPlan::go_dense), for the
+// passes and counts that follow too: the pivots here say nothing of det T then.
 #include <algorithm>
 
 #include "engine.hpp"
@@ -175,6 +176,7 @@ __global__ __launch_bounds__(kBdLuThreads) void k_bd_lu(const BdProb* __restrict
   const int st = bd_start(q, c), len = bd_start(q, c + 1) - 1 - st;
   const c128* __restrict__ f = na.fz + (long long)g * kMaxTerms;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!D.active) return;  // (its problem is factored densely now; also below)
   if (c == 0 && tid == 0) info[g] = D.n;  // a zero pivot here is left to the refinement
 
   constexpr int H = B / 2;
@@ -421,6 +423,7 @@ __global__ __launch_bounds__(kBdSolveThreads) void k_bd_solve(const BdProb* __re
   const int s = find_slot(prefix, cnt, v);
   const BdProb& q = bp[s];
   const ProbDesc& D = pd[q.prob];
+  if (rhs == 0 && !D.active) return;
   const int tiles = rhs == 0 ? q.wc / B : q.Lp / B;
   int t = v - prefix[s];
   const int j = t / (q.nch * tiles);
@@ -570,6 +573,7 @@ __global__ __launch_bounds__(256) void k_bd_hprod(const BdProb* __restrict__ bp,
   const int s = find_slot(prefix, cnt, v);
   const BdProb& q = bp[s];
   const ProbDesc& D = pd[q.prob];
+  if (rhs == 0 && !D.active) return;
   const int os = rhs == 0 ? q.wc : q.Lp, tiles = os / B, hb = (q.rp + 127) / 128;
   int t = v - prefix[s];
   const int j = t / (q.nch * tiles * hb);
@@ -651,6 +655,7 @@ __global__ __launch_bounds__(256) void k_bd_border(const BdProb* __restrict__ bp
   const ProbDesc& D = pd[q.prob];
   const int ns = q.nch - 1, per = ns + q.rp / B;
   const int j = (v - prefix[s]) / per, grp = (v - prefix[s]) - j * per;
+  if (!D.active) return;
   const int g = D.node0 + j, b = q.b, tid = threadIdx.x;
   const c128* __restrict__ f = na.fz + (long long)g * kMaxTerms;
   c64* __restrict__ S = Sb + q.offS + (long long)j * q.strideS;

@@ -130,7 +130,6 @@ void solve_set_lg(SolvePlan& sp, int lg, int L);
 
 struct ProblemTables {
   Table assemble;  // element tiles per problem
-  Table assemble64;  // the same for an FP64 re-solve (bordered problems too)
   Table resid;       // residual GEMM tiles per problem with complex terms (64 x 64)
   Table resid_real;  // residual GEMM tiles per problem with real terms only (kResidRealTM x kResidRealTQ,
                      // or kResidBigTM x kResidBigTQ with resid_big)

@@ -406,6 +406,7 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
     srows = ((n + S - 1) / S + 31) / 32 * 32;
     S = (n + srows - 1) / srows;
   };
+  bound_ = probs;
   lr_jobs_.clear();
   size_t zoff = 0;
   for (int p = 0; p < nprob; ++p) {
@@ -448,7 +449,7 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
     D.zpts = q.zpts;
     D.fpts = q.zpts != nullptr ? q.fpts : nullptr;
     D.s_stride = q.s_stride > 0 ? q.s_stride : (long long)D.n * D.L;
-    D.active = 1;
+    D.active = gone_[p] ? 0 : 1;
   }
   NEP_TRY(upload_lr_jobs(kLrScratch, st));
   NEP_HIP(hipMemcpyAsync(dpd_.p, hpd_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
@@ -457,6 +458,24 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
 
 nep_status MomentsPlan::rebind(const std::vector<PlanProblem>& probs, hipStream_t st) {
   NEP_CHECK((int)probs.size() == nprob, NEP_ERR_ARG, "rebind: problem count changed");
+  // a rejection is one of the nodes: with other ones the bordered factors are tried again
+  for (int p = 0; p < nprob && n_dense_ > 0; ++p) {
+    const nep_contour &a = probs[p].g, &b = bound_[p].g;
+    const bool same = probs[p].op == bound_[p].op && probs[p].zpts == nullptr && bound_[p].zpts == nullptr &&
+                      a.kind == b.kind && a.c[0] == b.c[0] && a.c[1] == b.c[1] && a.rho == b.rho && a.v == b.v;
+    if (gone_[p] && !same) {
+      dense_.clear();
+      n_dense_ = 0;
+      gone_.assign(nprob, 0);
+    }
+  }
+  for (DenseSet& d : dense_) {
+    std::vector<PlanProblem> sub;
+    for (int p : d.prob) sub.push_back(probs[p]);
+    d.plan->opt.tol = opt.tol;
+    d.idle = false;
+    NEP_TRY(d.plan->rebind(sub, st));
+  }
   return upload_problems(probs, st);
 }
 
@@ -466,18 +485,39 @@ nep_status MomentsPlan::rebind_members(const std::vector<int>& member, const std
   NEP_CHECK(member.size() == V.size() && member.size() == S.size(), NEP_ERR_ARG, "rebind: size mismatch");
   NEP_CHECK(s_stride == nullptr || s_stride->size() == member.size(), NEP_ERR_ARG, "rebind: stride count");
   for (auto& D : hpd_) D.active = 0;
+  std::vector<int> at(nprob, -1);  // each problem's index in member
   for (size_t k = 0; k < member.size(); ++k) {
     const int p = member[k];
     NEP_CHECK(p >= 0 && p < nprob, NEP_ERR_ARG, "rebind: member %d out of range", p);
-    NEP_CHECK(!hpd_[p].active, NEP_ERR_ARG, "rebind: member %d bound twice", p);
+    NEP_CHECK(at[p] < 0, NEP_ERR_ARG, "rebind: member %d bound twice", p);
+    at[p] = (int)k;
     ProbDesc& D = hpd_[p];
-    D.active = 1;
+    D.active = gone_[p] ? 0 : 1;
     D.V = V[k];
     D.S = S[k];
     D.zpts = nullptr;
     D.fpts = nullptr;
     D.s_stride = s_stride != nullptr ? (*s_stride)[k] : (long long)D.n * D.L;
     NEP_CHECK(D.s_stride >= (long long)D.n * D.L, NEP_ERR_ARG, "rebind: moment stride below n*L");
+    bound_[p].V = V[k];
+    bound_[p].S = S[k];
+    bound_[p].s_stride = D.s_stride;
+  }
+  for (DenseSet& d : dense_) {
+    std::vector<int> mem;
+    std::vector<const c128*> dv;
+    std::vector<c128*> ds;
+    std::vector<long long> str;
+    for (size_t k = 0; k < d.prob.size(); ++k) {
+      const int p = d.prob[k];
+      if (at[p] < 0) continue;
+      mem.push_back((int)k);
+      dv.push_back(V[at[p]]);
+      ds.push_back(S[at[p]]);
+      str.push_back(hpd_[p].s_stride);
+    }
+    d.idle = mem.empty();
+    if (!d.idle) NEP_TRY(d.plan->rebind_members(mem, dv, ds, st, &str));
   }
   NEP_HIP(hipMemcpyAsync(dpd_.p, hpd_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
   return NEP_OK;
@@ -490,6 +530,77 @@ void MomentsPlan::release_fallback() {
   dT64_.release();
   ddinv64_.release();
   dlinv64_.release();
+  for (DenseSet& d : dense_) d.plan->release_fallback();
+}
+
+size_t MomentsPlan::dense_bytes() const {
+  size_t b = 0;
+  for (const DenseSet& d : dense_) b += d.plan->device_bytes();
+  return b;
+}
+
+nep_status MomentsPlan::enqueue_dense(hipStream_t st, bool eager, bool refactor) {
+  rejected_.assign(nprob, 0);
+  for (DenseSet& d : dense_)
+    if (!d.idle) NEP_TRY(d.plan->enqueue(st, eager, refactor));
+  return NEP_OK;
+}
+
+// Hands problems over to a dense set, and runs it.
+nep_status MomentsPlan::go_dense(const std::vector<int>& which, hipStream_t st) {
+  DenseSet d;
+  d.prob = which;
+  std::vector<PlanProblem> probs;
+  for (int p : which) probs.push_back(bound_[p]);
+  PlanOptions o = opt;
+  o.dense = true;
+  d.plan = std::make_unique<MomentsPlan>();
+  nep_status s = d.plan->build(probs, o, st);
+  if (s == NEP_ERR_OOM) {  // an arena without room: take the rare case from the device heap
+    ArenaScope heap(nullptr);
+    d.plan = std::make_unique<MomentsPlan>();
+    s = d.plan->build(probs, o, st);
+  }
+  NEP_TRY(s);
+  NEP_TRY(d.plan->enqueue(st, true));
+  for (int p : which) {
+    gone_[p] = 1;
+    hpd_[p].active = 0;
+  }
+  n_dense_ += (int)which.size();
+  dense_.push_back(std::move(d));
+  NEP_HIP(hipMemcpyAsync(dpd_.p, hpd_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
+  return NEP_OK;
+}
+
+// After the refinement: the bordered problems with nodes left over go dense
+// (not those with a node on a pole or cut, which fail either way).  others: a
+// node of a dense or band problem is left over.
+nep_status MomentsPlan::reject_bordered(hipStream_t st, bool& others) {
+  std::vector<int> conv(nnodes), bad(nnodes), which;
+  NEP_HIP(hipMemcpyAsync(conv.data(), ir_.conv, sizeof(int) * nnodes, hipMemcpyDeviceToHost, st));
+  NEP_HIP(hipMemcpyAsync(bad.data(), na_.bad, sizeof(int) * nnodes, hipMemcpyDeviceToHost, st));
+  NEP_HIP(hipStreamSynchronize(st));
+  others = false;
+  for (int p = 0; p < nprob; ++p) {
+    int left = 0, nbad = 0;
+    for (int g = hpd_[p].node0; g < hpd_[p].node0 + opt.N; ++g) {
+      left += conv[g] ? 0 : 1;
+      nbad += bad[g] ? 1 : 0;
+    }
+    if (!hpd_[p].bordered) {
+      others |= left > 0;
+    } else if (left > 0 && nbad == 0) {
+      rejected_[p] = left;
+      which.push_back(p);
+      for (int g = hpd_[p].node0; g < hpd_[p].node0 + opt.N; ++g) conv[g] = 1;
+    }
+  }
+  if (which.empty()) return NEP_OK;
+  NEP_TRY(go_dense(which, st));
+  NEP_HIP(hipMemcpyAsync(ir_.conv, conv.data(), sizeof(int) * nnodes, hipMemcpyHostToDevice, st));
+  NEP_HIP(hipStreamSynchronize(st));  // conv leaves scope
+  return NEP_OK;
 }
 
 nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanOptions& o, hipStream_t st) {
@@ -497,6 +608,10 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   nprob = (int)probs.size();
   Lmax = o.L;
   hpd_.assign(nprob, ProbDesc{});
+  dense_.clear();
+  n_dense_ = 0;
+  gone_.assign(nprob, 0);
+  rejected_.assign(nprob, 0);
   std::vector<int> hprob, hj;
   std::vector<MatDesc> all;
   std::vector<MatDesc> dense;
@@ -521,7 +636,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     D.offP = offP;
     D.offBW = offBW;
     {
-      // the refinement, and the dense FP64 re-solve behind it, have to be there
+      // the refinement, and the dense factors behind it, have to be there
       int rank, nch;
       D.bordered = !D.band && !o.dense && o.prec == NEP_PREC_C32_IR64 && o.max_refine > 0 && o.fallback &&
                    bordered_of(*probs[p].op, rank, nch) >= 0;
@@ -551,19 +666,6 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   }
   nnodes = g;
   t_elems_ = offT;
-  sorted64_ = dense;
-  for (int p = 0; p < nprob; ++p) {  // after the dense blocks, in the FP64 re-solve's buffer only
-    ProbDesc& D = hpd_[p];
-    if (!D.bordered) continue;
-    D.offT0 = offT;
-    for (int j = 0; j < o.N; ++j) {
-      MatDesc m = all[(size_t)D.node0 + j];
-      m.offT = offT + (long long)j * D.strideT;
-      sorted64_.push_back(m);
-    }
-    offT += (long long)o.N * D.strideT;
-  }
-  t64_elems_ = offT;
   w_elems_ = offW;
   y_elems_ = offY;
   rows_total_ = offRow;
@@ -574,16 +676,14 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   std::stable_sort(sorted_.begin(), sorted_.end(), larger);
   shapes_ = all;
   std::stable_sort(shapes_.begin(), shapes_.end(), larger);
-  std::stable_sort(sorted64_.begin(), sorted64_.end(), larger);
 
   lu_.build(sorted_, o.prec);
   const bool mixed = o.prec == NEP_PREC_C32_IR64;
 
   hprefix_.clear();
   SolvePlan_build(sp_, hprefix_, sorted_, o.L, o.prec, dinv_off_, dinv_elems_);
-  SolvePlan_build(sp64_, hprefix_, sorted64_, o.L, o.prec, dinv64_off_, dinv64_elems_);
   {
-    std::vector<int> ca, ca64, cr, crr, cm;
+    std::vector<int> ca, cr, crr, cm;
     // real-term residual tiles: the big ones when they still give every CU
     // two groups (they halve the operand traffic per product)
     long long big_tiles = 0;
@@ -595,14 +695,12 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     for (int p = 0; p < nprob; ++p) {
       const long long n = hpd_[p].n;
       const bool cplx = probs[p].op->a_cplx != 0, band = hpd_[p].band != 0;
-      ca64.push_back(band ? 0 : (int)ceil_div_ll(n * n, 256));
-      ca.push_back(hpd_[p].bordered ? 0 : ca64.back());
+      ca.push_back(band || hpd_[p].bordered ? 0 : (int)ceil_div_ll(n * n, 256));
       cr.push_back(band ? 0 : cplx ? ceil_div((int)n, 64) * ceil_div(2 * o.N * o.L, 64) : 0);
       crr.push_back(band || cplx ? 0 : ceil_div((int)n, rtm) * ceil_div(2 * o.N * o.L, rtq));
       cm.push_back(ceil_div((int)n * o.L, 256) * ceil_div(2 * o.K, 8));  // (row, column) blocks x moment groups
     }
     build_prefix(hprefix_, pt_.assemble, ca);
-    build_prefix(hprefix_, pt_.assemble64, ca64);
     build_prefix(hprefix_, pt_.resid, cr);
     build_prefix(hprefix_, pt_.resid_real, crr);
     build_prefix(hprefix_, pt_.moments, cm);
@@ -626,8 +724,6 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
   NEP_TRY(A(dbw_, o.prec == NEP_PREC_FP64 ? 0 : sizeof(c64) * (size_t)offBW));
   NEP_TRY(A(dpiv_, (size_t)offP));
   NEP_TRY(A(dpmin_, any_band_ || !bp_.empty() ? sizeof(double) * (size_t)nnodes : 0));
-  NEP_TRY(A(dmd64_, bp_.empty() ? 0 : sizeof(MatDesc) * sorted64_.size()));
-  NEP_TRY(A(ddinv64_off_, bp_.empty() ? 0 : sizeof(long long) * sorted64_.size()));
   if (sp_.nblk > 0) {  // right-hand sides of the blocked solve
     NEP_TRY(A(dW_, sizeof(c64) * (size_t)sp_.nblk * sp_.npad * sp_.L));
     sp_.W = dW_.as<c64>();
@@ -705,11 +801,6 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
 
   // pageable sources: each copy has taken its bytes when the call returns
   NEP_TRY(upload_bordered(st));
-  if (!bp_.empty()) {
-    NEP_HIP(hipMemcpyAsync(dmd64_.p, sorted64_.data(), sizeof(MatDesc) * sorted64_.size(), hipMemcpyHostToDevice, st));
-    NEP_HIP(hipMemcpyAsync(ddinv64_off_.p, dinv64_off_.data(), sizeof(long long) * dinv64_off_.size(),
-                           hipMemcpyHostToDevice, st));
-  }
   if (!sorted_.empty()) {
     NEP_HIP(hipMemcpyAsync(dmd_.p, sorted_.data(), sizeof(MatDesc) * sorted_.size(), hipMemcpyHostToDevice, st));
     NEP_HIP(hipMemcpyAsync(ddinv_off_.p, dinv_off_.data(), sizeof(long long) * dinv_off_.size(),
@@ -821,7 +912,11 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
         if (hcounter_[0] == 0) break;
       }
     }
-    if (eager && hcounter_[0] > 0 && opt.fallback && sizeof(P) == 4) NEP_TRY(run_fallback<double>(st));
+    if (eager && hcounter_[0] > 0 && opt.fallback && sizeof(P) == 4) {
+      bool others = true;
+      if (!bp_.empty()) NEP_TRY(reject_bordered(st, others));
+      if (others) NEP_TRY(run_fallback<double>(st));
+    }
   }
   NEP_HIP(launch_moments(pd, pre, pt_.moments, na_, Y, st));
   return NEP_OK;
@@ -837,9 +932,9 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   static_assert(sizeof(P) == 8, "fallback runs in FP64");
   if (!dT64_.p && !dF64_.p) {
     auto alloc64 = [&]() -> nep_status {
-      nep_status s = dT64_.alloc(sizeof(c128) * (size_t)t64_elems_);
-      if (s == NEP_OK) s = ddinv64_.alloc(sizeof(c128) * (size_t)dinv64_elems_);
-      if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted64_.size() * kLuMaxJB * kLuMaxJB);
+      nep_status s = dT64_.alloc(sizeof(c128) * (size_t)t_elems_);
+      if (s == NEP_OK) s = ddinv64_.alloc(sizeof(c128) * (size_t)dinv_elems_);
+      if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted_.size() * kLuMaxJB * kLuMaxJB);
       if (s == NEP_OK) s = dF64_.alloc(sizeof(c128) * (size_t)f_elems_);
       if (s == NEP_OK) s = dpiv64_.alloc(dpiv_.bytes);
       if (s == NEP_OK) s = dpmin64_.alloc(dpmin_.bytes);
@@ -861,7 +956,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_TRY(s);
   }
   const ProbDesc* pd = dpd_.as<ProbDesc>();
-  const MatDesc* md = bp_.empty() ? dmd_.as<MatDesc>() : dmd64_.as<MatDesc>();
+  const MatDesc* md = dmd_.as<MatDesc>();
   const int* pre = dprefix_.as<int>();
   c128* T = dT64_.as<c128>();
   const int* skip = ir_.conv;
@@ -873,9 +968,9 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     for (int p = 0; p < nprob; ++p)
       for (int j = 0; j < opt.N; ++j) fallback_count_[p] += conv[hpd_[p].node0 + j] ? 0 : 1;
   }
-  NEP_HIP(launch_assemble<double>(pd, pre, pt_.assemble64, na_, T, skip, st));
+  NEP_HIP(launch_assemble<double>(pd, pre, pt_.assemble, na_, T, skip, st));
   c128* Dinv = ddinv64_.as<c128>();
-  const long long* doff = bp_.empty() ? ddinv_off_.as<long long>() : ddinv64_off_.as<long long>();
+  const long long* doff = ddinv_off_.as<long long>();
   {
     // factor only the unconverged matrices: a compact plan over them (in the
     // size order of the full plan), whose diagonal-block inverses land where
@@ -885,10 +980,10 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_HIP(hipStreamSynchronize(st));
     std::vector<MatDesc> sub;
     std::vector<long long> sub_off;
-    for (size_t b = 0; b < sorted64_.size(); ++b)
-      if (!conv[sorted64_[b].node]) {
-        sub.push_back(sorted64_[b]);
-        sub_off.push_back(dinv64_off_[b]);
+    for (size_t b = 0; b < sorted_.size(); ++b)
+      if (!conv[sorted_[b].node]) {
+        sub.push_back(sorted_[b]);
+        sub_off.push_back(dinv_off_[b]);
       }
     if (!sub.empty()) {
       LuPlan lsub;
@@ -914,7 +1009,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   if (any_band_)
     NEP_HIP(band_factor<double>(bt_, pd, pre, na_, dF64_.as<c128>(), piv, dinfo_.as<int>(), dpmin64_.as<double>(),
                                 skip, st));
-  NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
+  NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
                             skip, ir_, st));
   if (any_band_)
     NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), nullptr, kBandV, skip, ir_,
@@ -928,7 +1023,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
     NEP_HIP(hipMemcpyAsync(hcounter_, ir_.counters, sizeof(int), hipMemcpyDeviceToHost, st));
     NEP_HIP(hipStreamSynchronize(st));
     if (hcounter_[0] == 0) break;
-    NEP_HIP(solve_run<double>(sp64_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
+    NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, dR_.as<c128>(), dY_.as<c128>(),
                               true, ir_.conv, ir_, st));
     if (any_band_)
       NEP_HIP(band_solve<double>(bt_, pd, pre, dF64_.as<c128>(), piv, dR_.as<c128>(), dY_.as<c128>(), nullptr, kBandRefine, ir_.conv,
@@ -974,6 +1069,8 @@ nep_status MomentsPlan::solve_rhs(hipStream_t st) {
 
 nep_status MomentsPlan::enqueue(hipStream_t st, bool eager, bool refactor) {
   fallback_pending_ = false;
+  NEP_TRY(enqueue_dense(st, eager, refactor));
+  if (all_dense()) return NEP_OK;
   if (opt.prec == NEP_PREC_FP64) return enqueue_t<double>(st, eager, refactor);
   return enqueue_t<float>(st, eager, refactor);
 }
@@ -981,6 +1078,23 @@ nep_status MomentsPlan::enqueue(hipStream_t st, bool eager, bool refactor) {
 template <typename P>
 hipError_t logdet_run(const MatDesc* md, int nmat, const cx<P>* T, const int* rows, int nnodes, double* out,
                       hipStream_t st);
+
+nep_status MomentsPlan::node_flags(hipStream_t st, std::vector<int>& info, std::vector<int>& bad) const {
+  info.resize(nnodes);
+  bad.resize(nnodes);
+  NEP_HIP(hipMemcpyAsync(info.data(), dinfo_.p, sizeof(int) * nnodes, hipMemcpyDeviceToHost, st));
+  NEP_HIP(hipMemcpyAsync(bad.data(), na_.bad, sizeof(int) * nnodes, hipMemcpyDeviceToHost, st));
+  NEP_HIP(hipStreamSynchronize(st));
+  for (const DenseSet& d : dense_) {
+    std::vector<int> di, db;
+    NEP_TRY(d.plan->node_flags(st, di, db));
+    for (size_t k = 0; k < d.prob.size(); ++k) {
+      std::copy_n(di.begin() + k * opt.N, opt.N, info.begin() + hpd_[d.prob[k]].node0);
+      std::copy_n(db.begin() + k * opt.N, opt.N, bad.begin() + hpd_[d.prob[k]].node0);
+    }
+  }
+  return NEP_OK;
+}
 
 nep_status MomentsPlan::logdet(hipStream_t st, std::vector<double>& logabs, std::vector<double>& arg) {
   DevMem out;
@@ -1007,12 +1121,20 @@ nep_status MomentsPlan::logdet(hipStream_t st, std::vector<double>& logabs, std:
   NEP_HIP(hipStreamSynchronize(st));
   logabs.assign(h.begin(), h.begin() + nnodes);
   arg.assign(h.begin() + nnodes, h.end());
+  for (const DenseSet& d : dense_) {
+    std::vector<double> dl, da;
+    NEP_TRY(d.plan->logdet(st, dl, da));
+    for (size_t k = 0; k < d.prob.size(); ++k) {
+      std::copy_n(dl.begin() + k * opt.N, opt.N, logabs.begin() + hpd_[d.prob[k]].node0);
+      std::copy_n(da.begin() + k * opt.N, opt.N, arg.begin() + hpd_[d.prob[k]].node0);
+    }
+  }
   return NEP_OK;
 }
 
 nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallback) {
   const int G = nnodes;
-  std::vector<int> info(G), conv(G), sweeps(G), bad(G), counters(4);
+  std::vector<int> info(G), conv(G, 1), sweeps(G), bad(G), counters(4);
   std::vector<double> rho(G);
   std::vector<double> pmin(G);
   auto read_back = [&]() -> nep_status {  // one gathered block, one copy
@@ -1035,13 +1157,14 @@ nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallba
     std::memcpy(counters.data(), iv + 4 * G, sizeof(int) * 4);
     return NEP_OK;
   };
-  NEP_TRY(read_back());
+  if (!all_dense()) NEP_TRY(read_back());
   const bool refined = opt.max_refine > 0;
   const bool mixed = opt.prec == NEP_PREC_C32_IR64;
-  std::vector<int> excluded;  // unconverged nodes of problems that fail anyway
+  std::vector<int> excluded;  // unconverged nodes of problems that fail anyway, or go dense
   if (allow_fallback && refined && mixed && opt.fallback && !fallback_pending_) {
     // A fixed-sweep run left nodes unconverged: re-solve them in FP64 and
-    // recompute the moments (the eager path does this inside enqueue).  The
+    // recompute the moments, or hand a bordered problem over to dense factors
+    // (the eager path does this inside enqueue).  The
     // decision is per problem: a problem with a node on a pole or cut, or an
     // exact zero pivot, fails whatever its other nodes do, so its nodes are
     // left out, and the other problems of the batch are re-solved exactly
@@ -1052,11 +1175,22 @@ nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallba
       if (bad[g] || info[g] < hpd_[p].n) fails[p] = 1;
     }
     bool any = false;
+    std::vector<int> reject;
     for (int g = 0; g < G; ++g) {
-      if (conv[g]) continue;
-      if (fails[na_prob_host_[g]]) excluded.push_back(g);
-      else any = true;
+      const int p = na_prob_host_[g];
+      if (conv[g] || gone_[p]) continue;
+      if (fails[p]) {
+        excluded.push_back(g);
+      } else if (hpd_[p].bordered) {
+        excluded.push_back(g);
+        if (rejected_[p]++ == 0) reject.push_back(p);
+      } else {
+        any = true;
+      }
     }
+    // (without memory for it they stay unconverged, as below)
+    if (!reject.empty() && go_dense(reject, st) != NEP_OK)
+      for (int p : reject) rejected_[p] = 0;
     // (if the FP64 workspace cannot be allocated the nodes stay unconverged
     // and their problems report NEP_ERR_REFINE)
     if (any) {
@@ -1105,6 +1239,17 @@ nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallba
       s.refine_sweeps = std::max(s.refine_sweeps, std::min(sweeps[g] - 1, opt.max_refine));
       if (!conv[g]) s.n_unconverged++;
       if (std::isfinite(rho[g])) s.max_rel_residual = std::max(s.max_rel_residual, rho[g]);
+    }
+  }
+  for (DenseSet& d : dense_) {
+    if (d.idle) continue;
+    RunResult r;
+    (void)d.plan->finish(st, r, allow_fallback);
+    NEP_CHECK(r.stats.size() == d.prob.size(), NEP_ERR_DEVICE, "status of the dense factors could not be read");
+    for (size_t k = 0; k < d.prob.size(); ++k) {
+      nep_ciss_stats& s = out.stats[d.prob[k]];
+      s = r.stats[k];
+      s.n_fallback = std::max(s.n_fallback, rejected_[d.prob[k]]);
     }
   }
   // per-problem status, in order of precedence

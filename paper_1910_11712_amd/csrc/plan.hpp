@@ -147,17 +147,23 @@ class MomentsPlan {
   nep_status enqueue(hipStream_t st, bool eager, bool refactor = true);
   // A replay of a captured enqueue was launched: the next finish() starts
   // from the graph's own state (no FP64 re-solve of this run done yet).
-  void replayed() {
+  // What the graph does not hold is enqueued on st (see DenseSet).
+  nep_status replayed(hipStream_t st) {
     fallback_pending_ = false;
     lu_timed_ = false;
+    return enqueue_dense(st, false, true);
   }
+  // Nothing is left of the plan itself to enqueue or replay: all its problems
+  // are factored by dense sets.
+  bool all_dense() const { return n_dense_ == nprob; }
+  size_t dense_bytes() const;  // device memory of the dense sets
   // Waits, reads back device status and fills per-problem stats.  With
   // allow_fallback, nodes that a fixed-sweep (non-eager) run left
   // unconverged are re-solved in FP64 and the moments recomputed (if the
   // options enable the fallback).
   nep_status finish(hipStream_t st, RunResult& out, bool allow_fallback);
   // Device buffers shared with extraction and the server.
-  const c128* Y() const { return dY_.as<c128>(); }
+  const c128* Y() const { return all_dense() && nprob == 1 ? dense_[0].plan->Y() : dY_.as<c128>(); }
   // Shifted solves on resident factors (a plan over explicit points or the
   // contour's nodes): factor() assembles and factors T at every node;
   // solve_rhs() then sets Y_j = T(z_j)^{-1} R_j for the right-hand sides the
@@ -167,7 +173,6 @@ class MomentsPlan {
   nep_status solve_rhs(hipStream_t st);
   c128* R_mut() { return dR_.as<c128>(); }
   c128* Y_mut() { return dY_.as<c128>(); }
-  const NodeArrays& nodes() const { return na_; }
   // The factors of the plan's first (largest) matrix, for solves outside the
   // batched solve kernels: its descriptor, the factor buffer, the row map and
   // its diagonal-block inverses ([block][0: L, 1: U][64][64], row-major).
@@ -178,6 +183,9 @@ class MomentsPlan {
   const int* row_map() const { return drows_.as<int>(); }
   const void* dinv0() const { return ddinv_.as<char>() + dinv_off_[0] * (opt.prec == NEP_PREC_FP64 ? 16 : 8); }
   const int* info() const { return dinfo_.as<int>(); }
+  // Per node, read back to the host: first zero pivot (or n), and whether it
+  // lies on a pole or cut.
+  nep_status node_flags(hipStream_t st, std::vector<int>& info, std::vector<int>& bad) const;
   // Per node (global index): log|det T(z_g)| and arg det T(z_g) in (-pi, pi]
   // from the resident factors (the product of the pivots and the sign of the
   // row permutation), read back to host arrays of nnodes entries.
@@ -215,7 +223,7 @@ class MomentsPlan {
   // Time one full moment pass (fixed sweeps, no host read-back) per rep on st
   // and return the median in ms (after one untimed pass).
   nep_status time_pass(hipStream_t st, int reps, float& ms);
-  size_t device_bytes() const { return total_bytes_; }
+  size_t device_bytes() const { return total_bytes_ + dense_bytes(); }
   static size_t estimate_bytes(int n, int N, int L, int prec);
 
   PlanOptions opt;
@@ -271,13 +279,24 @@ class MomentsPlan {
   int rowsb_total_ = 0;
   DevMem dbp_, dbd_[10], dmdb_, dpdb_, dlub_prefix_, drowsb_, drowsb_snap_, dinfob_, ddinvb_, ddinvb_off_, dlinvb_,
       darriveb_, dynormb_;
-  // an FP64 re-solve factors the bordered problems' nodes densely as well:
-  // the matrices, solve plan and tables of dense and bordered problems
-  std::vector<MatDesc> sorted64_;
-  SolvePlan sp64_;
-  std::vector<long long> dinv64_off_;
-  long long dinv64_elems_ = 0, t64_elems_ = 0;
-  DevMem dmd64_, ddinv64_off_;
+  // Bordered problems that the refinement rejected (a node of theirs did not
+  // reach the tolerance: a chunk is singular, or nearly so, where T is not)
+  // are handed to a plan over dense factors, which then takes their place for
+  // solves, determinants and status as long as their nodes stay the same:
+  // here they sit out (ProbDesc::active).
+  struct DenseSet {
+    std::unique_ptr<MomentsPlan> plan;
+    std::vector<int> prob;  // its problems, in its order
+    bool idle = false;      // none of them takes part in the current pass
+  };
+  std::vector<DenseSet> dense_;
+  int n_dense_ = 0;
+  std::vector<char> gone_;           // per problem: in a dense set
+  std::vector<int> rejected_;        // per problem: nodes rejected in the current pass
+  std::vector<PlanProblem> bound_;   // per problem: its operator and buffers (valid while it is active)
+  nep_status enqueue_dense(hipStream_t st, bool eager, bool refactor);
+  nep_status go_dense(const std::vector<int>& which, hipStream_t st);
+  nep_status reject_bordered(hipStream_t st, bool& others);
   std::vector<int> hprefix_;
   DevMem dpd_, dmd_, dprefix_, dlu_prefix_;
   DevMem dT_, drows_, drows_snap_, dinfo_, dY_, dR_, dnode_, dir_, dT64_, dW_;

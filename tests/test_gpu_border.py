@@ -6,6 +6,7 @@ oracle; further probes, counts and points against the dense path; a singular
 chunk of a nonsingular matrix; batches against single calls."""
 import numpy as np
 import pytest
+import scipy.linalg
 
 import oracle
 import workloads as wl
@@ -145,6 +146,105 @@ def test_batch_equals_single_calls(nep, graph):
         B.nep_batch_run(b, len(ops))
         for k in range(len(ops)):
             assert np.array_equal(nep.moments_to_numpy(Ss[k]), singles[k]), (rep, k)
+    B.nep_batch_destroy(b)
+    for op in ops:
+        op.close()
+
+
+def _weak_chunk(eps, n=416, twin=False):
+    """A - z D + W: row 100 of the banded part is eps times a random row at
+    every z, and the low-rank term W makes T regular there."""
+    rng = np.random.default_rng(4)
+    A = _problem(n, 5, []).mats[0].copy()
+    A[100] *= eps
+    D = np.eye(n)
+    D[100, 100] = 0.0
+    U, V = rng.standard_normal((n, 20)), rng.standard_normal((n, 20))
+    U[100] = 3.0 * rng.standard_normal(20)
+    if twin:
+        A[0, n - 1] += 1e-30
+    return Problem("weak", [A, D, 0.1 * U @ V.T],
+                   [wl.fn_rational([1.0]), wl.fn_rational([-1.0, 0.0]), wl.fn_rational([1.0])])
+
+
+@pytest.mark.parametrize("eps", [0.0, 1e-9, 1e-7, 1e-4])
+def test_count_behind_a_weak_chunk(nep, eps):
+    """det T by the argument principle where a chunk is singular or nearly so: the eigenvalues of the pencil inside."""
+    n, N, L = 416, 512, 2
+    p = _weak_chunk(eps)
+    lam = scipy.linalg.eigvals(p.mats[0] + p.mats[2], p.mats[1])
+    inside = int(np.sum(np.abs(lam[np.isfinite(lam)] - 5.05) < 0.7))
+    op, V, Sg, st = _moments(nep, p, N, L)
+    print(st)
+    assert st["n_unconverged"] == 0 and st["singular_node"] < 0 and st["min_abs_pivot"] > 0.0, st
+    B = nep.binding
+    c, step, w = B.nep_ciss_count(op.h)
+    opt, _, _, stt = _moments(nep, _weak_chunk(eps, twin=True), N, L)
+    assert stt["n_fallback"] == 0, stt
+    ct, stept, wt = B.nep_ciss_count(opt.h)
+    assert c == ct == inside and step < 3.0, (c, ct, inside, step, stept)
+    # the determinants stay usable after further probes, on the same factors
+    S2 = torch.empty((4, L, n), dtype=torch.complex128, device="cuda")
+    B.nep_ciss_moments_more(op.h, nep.device_probes(wl.probes(n, L, 9)), S2)
+    assert B.nep_ciss_count(op.h)[0] == inside
+    op.close()
+    opt.close()
+
+
+def test_rejected_operator_keeps_dense_factors(nep):
+    """The first call finds a chunk singular; the calls that follow on the same
+    nodes solve with the dense factors at once, other nodes start anew."""
+    n, N, L, K = 416, 16, 3, 2
+    p = _weak_chunk(0.0)
+    op, V, Sg, st = _moments(nep, p, N, L)
+    assert st["n_fallback"] == N and st["n_unconverged"] == 0, st
+    _close(Sg, oracle.ciss_moments(p, CON, N, K, V), V)
+    V2 = wl.probes(n, L, 9)
+    S2 = torch.zeros((2 * K, L, n), dtype=torch.complex128, device="cuda")
+    st2 = nep.binding.nep_ciss_moments_more(op.h, nep.device_probes(V2), S2)
+    assert st2["n_fallback"] == 0 and st2["n_unconverged"] == 0, st2
+    _close(nep.moments_to_numpy(S2), oracle.ciss_moments(p, CON, N, K, V2), V2)
+    S3, st3 = op.moments(CON, nep.device_probes(V2), N, L, K, prec="mixed")
+    assert st3["n_fallback"] == 0 and st3["ms_lu"] > 0.0 and st3["min_abs_pivot"] > 0.0, st3
+    assert torch.equal(S2, S3)
+    con = Contour.circle(4.0, 0.5)
+    S4, st4 = op.moments(con, nep.device_probes(V), N, L, K, prec="mixed")
+    assert st4["n_fallback"] == N and st4["n_unconverged"] == 0, st4
+    _close(nep.moments_to_numpy(S4), oracle.ciss_moments(p, con, N, K, V), V)
+    z = [4.1 + 0.3j, 6.0 - 0.2j, 5.5 + 1.0j]
+    Y = torch.empty((3, L, n), dtype=torch.complex128, device="cuda")
+    nep.binding.nep_solve_at(op.h, z, nep.device_probes(V), Y, prec="mixed")
+    for k, zk in enumerate(z):
+        ref = np.linalg.solve(p.mats[0] - zk * p.mats[1] + p.mats[2], V)
+        assert np.linalg.norm(Y[k].cpu().numpy().T - ref) <= 1e-10 * np.linalg.norm(ref)
+    op.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_with_rejected_operators(nep, graph):
+    """Two rejected operators beside dense ones of more and fewer rows, a band
+    operator and a sound bordered one, in passes that follow each other."""
+    N, L, K = 8, 5, 2
+    probs = [_problem(500, 6, [], dense_twin=True), _weak_chunk(0.0), _problem(150, 6, [], dense_twin=True),
+             _problem(300, 1, []), _weak_chunk(0.0, n=1040), _problem(420, 7, [20])]
+    weak = [1, 4]
+    ops = [nep.SplitOperator.from_problem(p) for p in probs]
+    V = [wl.probes(p.n, L, k) for k, p in enumerate(probs)]
+    So = [oracle.ciss_moments(p, CON, N, K, v) for p, v in zip(probs, V)]
+    Vs = [nep.device_probes(v) for v in V]
+    Ss = [torch.zeros((2 * K, L, p.n), dtype=torch.complex128, device="cuda") for p in probs]
+    B = nep.binding
+    b = B.nep_batch_create([op.h for op in ops], [CON] * len(ops), B.opts_struct(N, L, K, "mixed"), Vs, Ss,
+                           use_graph=graph)
+    for rep in range(4):
+        for S in Ss:
+            S.zero_()
+        torch.cuda.synchronize()
+        stats = B.nep_batch_run(b, len(ops))
+        for k in range(len(ops)):
+            assert stats[k]["n_fallback"] == (N if k in weak and rep == 0 else 0), (rep, k, stats[k])
+            assert stats[k]["n_unconverged"] == 0 and stats[k]["min_abs_pivot"] > 0.0, (rep, k, stats[k])
+            _close(nep.moments_to_numpy(Ss[k]), So[k], V[k])
     B.nep_batch_destroy(b)
     for op in ops:
         op.close()
