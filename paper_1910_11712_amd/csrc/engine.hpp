@@ -232,6 +232,7 @@ struct LrJob {
   int n, r, NL;
   c128* Zp;         // S partial sums of Z (S x r x NL), used when S > 1
   int S, srows;     // the sum over s cut into S ranges of srows rows
+  int prob;         // its problem: nothing is read of one that sits out the pass
 };
 // The terms in rounds whose partial sums fit their scratch together: jobs
 // first .. first + cnt - 1, with the prefix tables of their tiles and of their

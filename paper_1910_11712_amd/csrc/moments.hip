@@ -121,6 +121,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble(const ProbDesc* __rest
   if (v < 0) return;
   const int p = find_slot(prefix, cnt, v);
   const ProbDesc& D = pd[p];
+  if (!D.active) return;
   const long long e = (long long)(v - prefix[p]) * kAsmThreads + threadIdx.x;
   if (e >= (long long)D.n * D.n) return;
   if (D.a_cplx) assemble_elem<P, true>(D, na, e, T, skip);

@@ -421,7 +421,7 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
         int S, srows;
         lr_split(D.n, S, srows);
         lr_jobs_.push_back(LrJob{q.op->dLrH[i], dlrz_.as<c128>() + zoff, D.offY, D.n, rk, opt.N * opt.L, nullptr, S,
-                                 srows});
+                                 srows, p});
         zoff += (size_t)rk * opt.N * opt.L;
       }
     }

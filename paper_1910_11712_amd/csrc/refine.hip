@@ -340,7 +340,8 @@ __global__ __launch_bounds__(64 * WR * WQ, 4) void k_resid_real(const ProbDesc* 
 // 60 us or more whatever its size (24 operators with eight such terms, six
 // sweeps: 11.3 ms one after the other, 8.5 together).
 __global__ __launch_bounds__(256) void k_lr_z(const LrJob* __restrict__ jobs, const int* __restrict__ prefix, int cnt,
-                                              const c128* __restrict__ Yb, int total) {
+                                              const ProbDesc* __restrict__ pd, const c128* __restrict__ Yb,
+                                              int total) {
   constexpr int KC = 32;
   __shared__ __align__(16) double Hs[KC][66];
   __shared__ c128 Ys[KC][33];
@@ -348,6 +349,7 @@ __global__ __launch_bounds__(256) void k_lr_z(const LrJob* __restrict__ jobs, co
   if (v < 0) return;
   const int slot = find_slot(prefix, cnt, v);
   const LrJob& J = jobs[slot];
+  if (!pd[J.prob].active) return;
   v -= prefix[slot];
   const double* __restrict__ H = J.H;
   const c128* __restrict__ Y = Yb + J.offY;
@@ -401,9 +403,10 @@ __global__ __launch_bounds__(256) void k_lr_z(const LrJob* __restrict__ jobs, co
 // Z[i] = sum over sp = 0..S-1 of Zp[sp m + i], in that order (terms of one
 // range have no groups here).
 __global__ __launch_bounds__(256) void k_lr_zsum(const LrJob* __restrict__ jobs, const int* __restrict__ prefix,
-                                                 int cnt) {
+                                                 int cnt, const ProbDesc* __restrict__ pd) {
   const int slot = find_slot(prefix, cnt, blockIdx.x);
   const LrJob& J = jobs[slot];
+  if (!pd[J.prob].active) return;
   const long long m = (long long)J.r * J.NL, i = (long long)(blockIdx.x - prefix[slot]) * 256 + threadIdx.x;
   if (i >= m) return;
   const c128* __restrict__ Zp = J.Zp;
@@ -425,13 +428,13 @@ hipError_t resid_run(const ProbDesc* pd, const int* prefix, const Table& t, cons
                      const NodeArrays& na, const c128* Y, c128* R, IrState ir, int /*nnodes*/, hipStream_t st,
                      const LrTables& lr) {
   for (const LrTables::Round& q : lr.rounds) {  // Z = H^T Y of every low-rank term, before the products that use it
-    hipLaunchKernelGGL(k_lr_z, dim3(xcd_grid(q.tiles)), dim3(256), 0, st, lr.jobs + q.first, lr.prefix + q.off, q.cnt, Y,
-                       q.tiles);
+    hipLaunchKernelGGL(k_lr_z, dim3(xcd_grid(q.tiles)), dim3(256), 0, st, lr.jobs + q.first, lr.prefix + q.off, q.cnt, pd,
+                       Y, q.tiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (q.sums > 0) {
       hipLaunchKernelGGL(k_lr_zsum, dim3(q.sums), dim3(256), 0, st, lr.jobs + q.first, lr.prefix + q.off + q.cnt + 1,
-                         q.cnt);
+                         q.cnt, pd);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -270,3 +270,36 @@ def test_server_probe_pool_augments_saturated_query(nep, prec):
     for o in oops:
         o.close()
     op.close()
+
+
+def test_resident_factors_outlive_a_neighbours_operator(nep):
+    """Two operators with low-rank terms factored in one batch; one handle is
+    destroyed, and further probes on the other's resident factors read
+    nothing of it."""
+    n, N, L, K, me = 400, 16, 4, 2, 16
+    con = Contour.circle(5.05, 0.05)
+
+    def problem(seed):
+        rng = np.random.default_rng(seed)
+        U, W = rng.standard_normal((n, 20)), rng.standard_normal((20, n))
+        return Problem("lowrank", [np.diag(np.linspace(1.0, 10.0, n)), np.eye(n), 0.01 * U @ W],
+                       [wl.fn_rational([1.0]), wl.fn_rational([-1.0, 0.0]), wl.fn_exp(alpha=0.1)])
+
+    pa, pb, plug = problem(1), problem(2), wl.delay_problem(600, tau=1.0, seed=7)
+    a, b, op = (nep.SplitOperator.from_problem(p) for p in (pa, pb, plug))
+    V, V2 = wl.probes(n, L, 5), wl.probes(n, L, 6)
+    ref = _alone(nep, b, con, V2, N, L, K, "mixed", me)
+    srv = nep.Server(hbm_budget=1 << 30, max_inflight=16, nstreams=1)
+    try:
+        t0 = srv.submit(op, Contour.circle(-1.0, 0.4), wl.probes(600, 8, 20), 32, 8, 4)  # the next two queue behind it
+        ta, tb = srv.submit(a, con, V, N, L, K, max_eigs=me), srv.submit(b, con, V, N, L, K, max_eigs=me)
+        srv.wait(t0)
+        ra, rb = srv.wait(ta), srv.wait(tb)
+        a.close()
+        again = srv.wait(srv.submit(b, con, V2, N, L, K, max_eigs=me))
+    finally:
+        srv.close()
+    assert ra["status"] == 0 and rb["status"] == 0 and again["status"] == 0
+    assert again["reused"] and np.array_equal(again["lam"], ref["lam"]) and np.array_equal(again["eta"], ref["eta"])
+    b.close()
+    op.close()
