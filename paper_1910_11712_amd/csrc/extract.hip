@@ -27,7 +27,7 @@
 namespace nep {
 
 struct ExtractWork {
-  DevMem B0, B1, tau, V0, P, smat, X0, Rt, fz, Rp, Ur, sw, G, wy;
+  DevMem B0, B1, tau, V0, P, smat, X0, Rt, fz, Rp, Ur, sw, wy;
   size_t cap_rows = 0, cap_cols = 0;
 };
 
@@ -949,14 +949,14 @@ nep_status extract_strided(Split& h, const nep_contour* g, const nep_ciss_opts* 
   NEP_CHECK(m <= e->max_eigs, NEP_ERR_ARG, "rank %d exceeds max_eigs %d", m, e->max_eigs);
   // V0 = Q [Ur0; 0]
   NEP_TRY(grow(w.V0, sizeof(c128) * M * m));
-  NEP_TRY(grow(w.G, sizeof(c128) * (size_t)KL * KL));
   NEP_TRY(grow(w.wy, sizeof(c128) * (size_t)KL * m));
   c128* V0 = w.V0.as<c128>();
   {
     const int nt = ceil_div(KL, 4);
-    hipLaunchKernelGGL(k_wy_gram, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, B0, M, KL, w.G.as<c128>());
+    c128* G = w.Rp.as<c128>();  // (the packed R has been read)
+    hipLaunchKernelGGL(k_wy_gram, dim3(nt * (nt + 1) / 2), dim3(256), 0, st, B0, M, KL, G);
     hipLaunchKernelGGL(k_wy_coef, dim3(m), dim3(std::min(kWyRows, ceil_div(KL, 64) * 64)), 0, st, B0, M, KL, tau,
-                       w.G.as<c128>(), Ur, w.wy.as<c128>());
+                       G, Ur, w.wy.as<c128>());
     NEP_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_wy_apply, dim3((unsigned)ceil_div_ll(M, 256), ceil_div(m, 8)), dim3(256), 0, st, B0, M, KL, m,
                        Ur, w.wy.as<c128>(), V0);

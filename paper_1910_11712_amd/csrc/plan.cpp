@@ -162,7 +162,7 @@ static int pad_ld(int n) {
 
 static size_t elem_size(int prec) { return prec == NEP_PREC_FP64 ? sizeof(c128) : sizeof(c64); }
 
-size_t MomentsPlan::estimate_bytes(int n, int N, int L, int prec) {
+size_t MomentsPlan::dense_bytes_of(int n, int N, int L, int prec) {
   const size_t ld = pad_ld(n);
   size_t b = (size_t)N * ld * n * elem_size(prec);        // factors
   b += (size_t)N * n * sizeof(int);                        // row maps
@@ -219,6 +219,74 @@ static int bordered_of(const SplitOperator& op, int& rank, int& nch) {
   return op.n >= std::max(kBdMinN, kBdMinRatio * b) ? w : -1;
 }
 
+// The bordered path's sizes of one problem.
+static BdProb bordered_sizes(const SplitOperator& op, int L) {
+  BdProb q{};
+  int rank;
+  q.w = bordered_of(op, rank, q.nch);
+  q.nb = ceil_div(op.n, kBdBlk);
+  q.rp = ceil_div(rank, kBdBlk) * kBdBlk;
+  q.wc = 2 * kBdBlk + q.rp;
+  q.Lp = ceil_div(L, kBdBlk) * kBdBlk;
+  q.pw = std::max(q.wc, q.Lp);
+  q.b = (q.nch - 1) * kBdBlk + q.rp;
+  q.ldS = pad_ld(std::max(1, q.b));
+  q.strideS = (long long)q.ldS * q.b;
+  return q;
+}
+
+// The refinement, and the dense factors behind it, have to be there.
+static bool takes_border(const SplitOperator& op, const PlanOptions& o) {
+  int rank, nch;
+  return !o.dense && o.prec == NEP_PREC_C32_IR64 && o.max_refine > 0 && o.fallback && band_of(op) == 0 &&
+         bordered_of(op, rank, nch) >= 0;
+}
+
+// Z = H^T Y of a low-rank term sums over the problem's n rows: cut into S
+// ranges (at most 16, at least 256 rows each, a multiple of 32) so that enough
+// groups run.
+static void lr_split(int n, int& S, int& srows) {
+  S = std::max(1, std::min(16, n / 256));
+  srows = ((n + S - 1) / S + 31) / 32 * 32;
+  S = (n + srows - 1) / srows;
+}
+
+// All terms run in one launch while their partial sums fit kLrScratch elements
+// (1 GiB), in rounds beyond.
+constexpr size_t kLrScratch = (size_t)1 << 26;
+
+size_t MomentsPlan::estimate_bytes(const SplitOperator& op, const PlanOptions& o) {
+  const size_t n = op.n, N = o.N, L = o.L, c8 = sizeof(c64), c16 = sizeof(c128), es = elem_size(o.prec);
+  size_t b = dense_bytes_of(op.n, o.N, o.L, o.prec);
+  // common to all paths: row maps, Y and R, node data
+  const size_t common = 2 * N * n * sizeof(int) + 2 * n * N * L * c16 +
+                        N * (kMaxTerms + kMaxMoments + 8) * c16 + N * kNormStride * 16;
+  const int w = o.dense ? 0 : band_of(op);
+  if (w > 0) {
+    b = std::max(b, common + N * n * (es * band_entries(w) + 1 + (es == c8 ? L * c8 : 0)));
+  } else if (takes_border(op, o)) {
+    const BdProb q = bordered_sizes(op, o.L);
+    const size_t nb = q.nb, rows = nb * kBdBlk, bl2 = kBdBlk * kBdBlk, nch = q.nch, bb = q.b, sS = q.strideS;
+    b = std::max(b, common + c8 * N * (nb * 5 * bl2 + rows * (q.wc + q.Lp + 1) + nch * q.rp * q.pw +
+                                       (nch - 1) * 2 * bl2 + sS) +
+                        N * rows * 2 + 2 * c16 * bb * N * L + 2 * N * bb * sizeof(int) +
+                        N * ((bb + 63) / 64) * 2 * 64 * 64 * c8 + (bb > 0 ? 2 * c8 * N * kLuMaxJB * kLuMaxJB : 0) +
+                        N * kNormStride * 8);
+  }
+  if (!op.a_cplx) {  // Z of the low-rank terms and their partial sums
+    size_t z = 0, part = 0;
+    for (int i = 0; i < op.ell; ++i) {
+      if (op.lr_rank[i] == 0) continue;
+      int S, srows;
+      lr_split(op.n, S, srows);
+      z += (size_t)op.lr_rank[i] * N * L;
+      if (S > 1) part += (size_t)S * op.lr_rank[i] * N * L;
+    }
+    b += c16 * (z + std::min(part, kLrScratch));
+  }
+  return b;
+}
+
 nep_status MomentsPlan::build_bordered(const std::vector<PlanProblem>& probs) {
   bp_.clear();
   hpdb_.assign(nprob, ProbDesc{});
@@ -228,18 +296,8 @@ nep_status MomentsPlan::build_bordered(const std::vector<PlanProblem>& probs) {
   for (int p = 0; p < nprob; ++p) {
     ProbDesc& D = hpd_[p];
     if (!D.bordered) continue;
-    BdProb q{};
-    int rank;
+    BdProb q = bordered_sizes(*probs[p].op, D.L);
     q.prob = p;
-    q.w = bordered_of(*probs[p].op, rank, q.nch);
-    q.nb = ceil_div(D.n, kBdBlk);
-    q.rp = ceil_div(rank, kBdBlk) * kBdBlk;
-    q.wc = 2 * kBdBlk + q.rp;
-    q.Lp = ceil_div(D.L, kBdBlk) * kBdBlk;
-    q.pw = std::max(q.wc, q.Lp);
-    q.b = (q.nch - 1) * kBdBlk + q.rp;
-    q.ldS = pad_ld(std::max(1, q.b));
-    q.strideS = (long long)q.ldS * q.b;
     q.offRowS = rowsb_total_;
     const long long N = D.N, bl2 = kBdBlk * kBdBlk;
     q.offB = oB;
@@ -396,16 +454,6 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
     if (!probs[p].op->a_cplx)
       for (int i = 0; i < probs[p].op->ell; ++i) zelems += (size_t)probs[p].op->lr_rank[i] * opt.N * opt.L;
   if (zelems > 0 && dlrz_.bytes < sizeof(c128) * zelems) NEP_TRY(dlrz_.alloc(sizeof(c128) * zelems));
-  // Z = H^T Y sums over the problem's n rows: cut into S ranges (at most 16,
-  // at least 256 rows each, a multiple of 32) so that enough groups run.  All
-  // terms run in one launch while their partial sums fit kLrScratch elements
-  // of dlrzp_ (1 GiB), in rounds beyond.
-  constexpr size_t kLrScratch = (size_t)1 << 26;
-  auto lr_split = [](int n, int& S, int& srows) {
-    S = std::max(1, std::min(16, n / 256));
-    srows = ((n + S - 1) / S + 31) / 32 * 32;
-    S = (n + srows - 1) / srows;
-  };
   bound_ = probs;
   lr_jobs_.clear();
   size_t zoff = 0;
@@ -451,7 +499,9 @@ nep_status MomentsPlan::upload_problems(const std::vector<PlanProblem>& probs, h
     D.s_stride = q.s_stride > 0 ? q.s_stride : (long long)D.n * D.L;
     D.active = gone_[p] ? 0 : 1;
   }
-  NEP_TRY(upload_lr_jobs(kLrScratch, st));
+  nep_status ls = upload_lr_jobs(kLrScratch, st);
+  if (ls == NEP_ERR_OOM) ls = upload_lr_jobs(0, st);  // no room for all at once: a term a round
+  NEP_TRY(ls);
   NEP_HIP(hipMemcpyAsync(dpd_.p, hpd_.data(), sizeof(ProbDesc) * nprob, hipMemcpyHostToDevice, st));
   return NEP_OK;
 }
@@ -635,12 +685,7 @@ nep_status MomentsPlan::build(const std::vector<PlanProblem>& probs, const PlanO
     D.offF = offF;
     D.offP = offP;
     D.offBW = offBW;
-    {
-      // the refinement, and the dense factors behind it, have to be there
-      int rank, nch;
-      D.bordered = !D.band && !o.dense && o.prec == NEP_PREC_C32_IR64 && o.max_refine > 0 && o.fallback &&
-                   bordered_of(*probs[p].op, rank, nch) >= 0;
-    }
+    D.bordered = takes_border(*probs[p].op, o);
     for (int j = 0; j < o.N; ++j, ++g) {
       MatDesc m;
       m.n = n;

@@ -224,7 +224,12 @@ class MomentsPlan {
   // and return the median in ms (after one untimed pass).
   nep_status time_pass(hipStream_t st, int reps, float& ms);
   size_t device_bytes() const { return total_bytes_ + dense_bytes(); }
-  static size_t estimate_bytes(int n, int N, int L, int prec);
+  // Device memory of one problem's share of a plan: what it takes on the path
+  // that build() chooses, or what dense factors take where that is more (a
+  // rejected bordered problem and an FP64 re-solve take those).  dense_bytes_of
+  // is the price of dense factors alone.
+  static size_t estimate_bytes(const SplitOperator& op, const PlanOptions& o);
+  static size_t dense_bytes_of(int n, int N, int L, int prec);
 
   PlanOptions opt;
   int nprob = 0, nnodes = 0, Lmax = 0;

@@ -84,6 +84,7 @@ struct Resident {
   std::vector<char> valid;  // the member's last query succeeded
   size_t bytes = 0;         // counted against the budget
   double last_use = 0.0;
+  size_t dense = 0;         // of it, dense sets of the plan
   bool out = false;         // a slot runs a pass on it
 };
 
@@ -109,7 +110,8 @@ struct Slot {
 
 bool same_batch(const Query& a, const Query& b) {
   return a.po.N == b.po.N && a.po.L == b.po.L && a.po.K == b.po.K && a.po.prec == b.po.prec &&
-         a.po.max_refine == b.po.max_refine && a.po.fallback == b.po.fallback && a.po.tol == b.po.tol;
+         a.po.max_refine == b.po.max_refine && a.po.fallback == b.po.fallback && a.po.tol == b.po.tol &&
+         a.po.dense == b.po.dense;
 }
 
 }  // namespace
@@ -169,8 +171,7 @@ size_t Server::query_buffer_bytes(const Query& q) {
 }
 
 size_t Server::query_bytes(const Query& q) {
-  return MomentsPlan::estimate_bytes(q.n, q.po.N, q.po.L, q.po.prec) + query_buffer_bytes(q) +
-         (1u << 20);  // tables, alignment
+  return MomentsPlan::estimate_bytes(q.h->impl.op, q.po) + query_buffer_bytes(q) + (1u << 20);  // tables, alignment
 }
 
 Resident* Server::find_resident(const Key& k, int* member) {
@@ -258,9 +259,18 @@ nep_status Server::submit(nep_split h, const nep_contour* g, const nep_ciss_opts
   q->eta = eta;
   q->inside = inside;
   q->X = X;
+  // Refused where dense factors do not fit.  Beyond that a price can exceed the
+  // budget by the bordered factors of a few hundred rows, which take more than
+  // dense ones (then those), or by the partial sums of low-rank terms (which do
+  // with less).
+  const size_t least = MomentsPlan::dense_bytes_of(q->n, q->po.N, q->po.L, q->po.prec) + q->fbytes + (1u << 20);
+  NEP_CHECK(least <= budget_, NEP_ERR_BUSY, "query needs %zu bytes, more than the server's HBM budget %zu", least,
+            budget_);
   q->bytes = query_bytes(*q);
-  NEP_CHECK(q->bytes <= budget_, NEP_ERR_BUSY, "query needs %zu bytes, more than the server's HBM budget %zu",
-            q->bytes, budget_);
+  if (q->bytes > budget_) {
+    q->po.dense = true;
+    q->bytes = std::min(query_bytes(*q), budget_);
+  }
   const size_t cnt = (size_t)q->n * q->Lmax;
   q->V.assign(static_cast<const c128*>(V), static_cast<const c128*>(V) + cnt);
   {
@@ -575,6 +585,10 @@ void Server::keep_resident(Slot& s, const std::vector<nep_status>& status) {
   const double t = clock();
   if (s.res != nullptr) {
     for (size_t k = 0; k < s.member.size(); ++k) s.res->valid[s.member[k]] = status[k] == NEP_OK;
+    const size_t dense = s.res->plan->dense_bytes();
+    resident_bytes_ += dense - s.res->dense;
+    s.res->bytes += dense - s.res->dense;
+    s.res->dense = dense;
     s.res->out = false;
     s.res->last_use = t;
     s.res = nullptr;
@@ -591,6 +605,8 @@ void Server::keep_resident(Slot& s, const std::vector<nep_status>& status) {
     r->bytes += s.q[k]->bytes - s.q[k]->fbytes;
   }
   s.own->release_fallback();
+  r->dense = s.own->dense_bytes();
+  r->bytes += r->dense;
   r->plan = std::move(s.own);
   r->last_use = t;
   resident_bytes_ += r->bytes;

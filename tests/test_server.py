@@ -4,6 +4,8 @@ A query's result must not depend on what else is in flight: every query run
 in a mix equals the same query run alone (moments + extraction on its own
 handle), bit for bit, and matches the oracle's eigenvalues inside the
 contour."""
+import re
+
 import numpy as np
 import pytest
 
@@ -276,13 +278,13 @@ def test_resident_factors_outlive_a_neighbours_operator(nep):
     """Two operators with low-rank terms factored in one batch; one handle is
     destroyed, and further probes on the other's resident factors read
     nothing of it."""
-    n, N, L, K, me = 400, 16, 4, 2, 16
-    con = Contour.circle(5.05, 0.05)
+    n, N, L, K, me = 400, 256, 4, 2, 16
+    con = Contour.circle(5.05, 0.027)
 
     def problem(seed):
         rng = np.random.default_rng(seed)
         U, W = rng.standard_normal((n, 20)), rng.standard_normal((20, n))
-        return Problem("lowrank", [np.diag(np.linspace(1.0, 10.0, n)), np.eye(n), 0.01 * U @ W],
+        return Problem("lowrank", [np.diag(np.linspace(1.0, 10.0, n)), np.eye(n), 1e-5 * U @ W],
                        [wl.fn_rational([1.0]), wl.fn_rational([-1.0, 0.0]), wl.fn_exp(alpha=0.1)])
 
     pa, pb, plug = problem(1), problem(2), wl.delay_problem(600, tau=1.0, seed=7)
@@ -302,4 +304,39 @@ def test_resident_factors_outlive_a_neighbours_operator(nep):
     assert ra["status"] == 0 and rb["status"] == 0 and again["status"] == 0
     assert again["reused"] and np.array_equal(again["lam"], ref["lam"]) and np.array_equal(again["eta"], ref["eta"])
     b.close()
+    op.close()
+
+
+def test_server_prices_the_path_that_a_query_takes(nep):
+    """n = 256 with two rank-32 terms: the band-and-border factors take more
+    memory than dense ones, and a budget that holds the dense ones serves the
+    query, as one that holds both does."""
+    n, N, L, K, me = 256, 512, 4, 2, 16
+    rng = np.random.default_rng(8)
+    con = Contour.circle(5.05, 0.03)
+    W = [1e-5 * rng.standard_normal((n, 32)) @ rng.standard_normal((32, n)) for _ in range(2)]
+    p = Problem("lowrank", [np.diag(np.linspace(1.0, 10.0, n)), np.eye(n)] + W,
+                [wl.fn_rational([1.0]), wl.fn_rational([-1.0, 0.0]), wl.fn_exp(alpha=0.1), wl.fn_rational([1.0])])
+    V = wl.probes(n, L, 5)
+    op = nep.SplitOperator.from_problem(p)
+    S, st = op.moments(con, nep.device_probes(V), N, L, K)
+    assert st["n_fallback"] == 0 and st["n_unconverged"] == 0, st
+    ref = op.extract(con, S, N, L, K, max_eigs=me)
+
+    def run(budget):
+        srv = nep.Server(hbm_budget=budget, max_inflight=4, nstreams=1)
+        try:
+            return srv.wait(srv.submit(op, con, V, N, L, K, max_eigs=me))
+        finally:
+            srv.close()
+
+    with pytest.raises(nep.binding.NepError) as e:
+        run(8 << 20)
+    least = int(re.search(r"needs (\d+) bytes", str(e.value)).group(1))
+    for budget in (least + (4 << 20), 4 * least):  # (the Z of the low-rank terms: 2 MiB)
+        r = run(budget)
+        assert r["status"] == 0, (budget, r["status"])
+        got, want = r["lam"][r["inside"]], ref["lam"][ref["inside"]]
+        assert len(got) == len(want) > 0
+        assert np.max(np.abs(got - want)) <= 1e-9
     op.close()
