@@ -892,11 +892,10 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   cx<P>* Dinv = ddinv_.as<cx<P>>();
   const long long* doff = ddinv_off_.as<long long>();
   hipStream_t beside = beside_;
-  if (beside != nullptr) {
-    // a captured pass keeps everything on st: with the bordered chain forked
-    // beside the dense LU, which forks by itself, hipStreamEndCapture ended in
-    // a host fault.  Why is not known, so band problems, which would be
-    // captured in the same arrangement, stay on st as well.
+  if (beside != nullptr && !bp_.empty()) {
+    // a captured pass keeps the bordered problems on st: a captured fork of
+    // their chain beside the dense LU's own forks ended in a fault of the
+    // runtime when the graph was made
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     NEP_HIP(hipStreamIsCapturing(st, &cs));
     if (cs != hipStreamCaptureStatusNone) beside = nullptr;
