@@ -893,46 +893,62 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   const long long* doff = ddinv_off_.as<long long>();
   hipStream_t beside = beside_;
   if (beside != nullptr && !bp_.empty()) {
-    // a captured pass keeps the bordered problems on st: a captured fork of
-    // their chain beside the dense LU's own forks ended in a fault of the
-    // runtime when the graph was made
+    // A captured pass keeps the bordered problems on st.  What was captured
+    // when hipStreamEndCapture ended in a host fault is the bordered chain on a
+    // forked stream with a further fork inside, the look-ahead of its border's
+    // LU; why the runtime fails there is not known.  So under capture streams
+    // are forked off st and joined to st alone, as the dense LU's own two and
+    // the band chain's are, which fork nothing themselves.
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     NEP_HIP(hipStreamIsCapturing(st, &cs));
     if (cs != hipStreamCaptureStatusNone) beside = nullptr;
   }
+  // What runs on the second stream is joined where st needs it: the bordered
+  // problems' solutions before the residual (one launch with the dense ones'),
+  // the band problems', whose residual follows on that stream, before the
+  // refinement test; their first solve follows their factorization without
+  // waiting for the dense ones.  (Joined after every step, with the band
+  // residual on st, small batches paid for it: 4 mixed problems of 64..128 rows
+  // 795 us a pass, 684 now, 648 with every problem dense; 10 of them 875, 749
+  // and 870.)
+  bool out = false;  // there is work that st has not joined
+  auto fork = [&]() -> nep_status {
+    if (beside == nullptr || out) return NEP_OK;
+    out = true;
+    NEP_HIP(hipEventRecord(ev_beside_[0], st));
+    NEP_HIP(hipStreamWaitEvent(beside, ev_beside_[0], 0));
+    return NEP_OK;
+  };
+  auto join = [&]() -> nep_status {
+    if (!out) return NEP_OK;
+    out = false;
+    NEP_HIP(hipEventRecord(ev_beside_[1], beside));
+    NEP_HIP(hipStreamWaitEvent(st, ev_beside_[1], 0));
+    return NEP_OK;
+  };
+  hipStream_t sx = beside != nullptr ? beside : st;
   if (refactor) {  // otherwise the factors (and info) of the previous pass are reused
     if (eager) NEP_HIP(hipEventRecord(ev_lu_[0], st));
-    if (beside != nullptr) {
-      NEP_HIP(hipEventRecord(ev_beside_[0], st));
-      NEP_HIP(hipStreamWaitEvent(beside, ev_beside_[0], 0));
-      NEP_TRY(structured_factor<P>(beside));
-      NEP_HIP(hipEventRecord(ev_beside_[1], beside));
-    }
+    NEP_TRY(fork());
+    if (beside != nullptr) NEP_TRY(structured_factor<P>(beside));
     NEP_HIP(lu_run<P>(lu_, md, dlu_prefix_.as<int>(), T, rows, drows_snap_.as<int>(), rows_total_, info, nullptr,
                       dlinv_.as<cx<P>>(), Dinv, doff, darrive_.as<int>(), st, ls_));
-    if (beside != nullptr) NEP_HIP(hipStreamWaitEvent(st, ev_beside_[1], 0));
-    else NEP_TRY(structured_factor<P>(st));
+    if (beside == nullptr) NEP_TRY(structured_factor<P>(st));
     if (eager) {
+      NEP_TRY(join());
       NEP_HIP(hipEventRecord(ev_lu_[1], st));
       lu_timed_ = true;
     }
   }
   // nodes of problems sitting out the pass are marked converged by k_coef
   auto solve = [&](bool refine) -> nep_status {
-    hipStream_t sx = beside != nullptr ? beside : st;
-    if (sx != st) {
-      NEP_HIP(hipEventRecord(ev_beside_[0], st));
-      NEP_HIP(hipStreamWaitEvent(sx, ev_beside_[0], 0));
-    }
+    NEP_TRY(fork());
     if (any_band_)
       NEP_HIP(band_solve<P>(bt_, pd, pre, dF_.as<cx<P>>(), piv, R, Y, dbw_.as<cx<P>>(), refine ? kBandRefine : kBandV, ir_.conv, ir_,
                             sx));
     if (!bp_.empty()) NEP_TRY(bordered_solve(refine, sx));
     NEP_HIP(solve_run<P>(sp_, pd, md, na_, T, rows, Dinv, doff, refine ? R : nullptr, Y, refine, ir_.conv, ir_, st));
-    if (sx != st) {
-      NEP_HIP(hipEventRecord(ev_beside_[1], sx));
-      NEP_HIP(hipStreamWaitEvent(st, ev_beside_[1], 0));
-    }
+    if (!bp_.empty()) NEP_TRY(join());
     return NEP_OK;
   };
   NEP_TRY(solve(false));
@@ -943,8 +959,9 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
     // trip; nodes already converged skip the solve, which makes it a no-op
     // when the count turns out to be zero.
     for (int s = 0; s <= opt.max_refine; ++s) {
+      if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, Y, R, ir_, out ? beside : st));
       NEP_HIP(resid_run(pd, pre, pt_.resid, pt_.resid_real, pt_.resid_big, na_, Y, R, ir_, nnodes, st, lr_));
-      if (any_band_) NEP_HIP(band_resid(bt_, pd, pre, na_, Y, R, ir_, st));
+      NEP_TRY(join());
       NEP_HIP(ir_control(pd, na_, ir_, nnodes, s, opt.tol, st));
       sweeps_run_ = s;
       if (eager) {
@@ -957,12 +974,14 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
         if (hcounter_[0] == 0) break;
       }
     }
+    NEP_TRY(join());
     if (eager && hcounter_[0] > 0 && opt.fallback && sizeof(P) == 4) {
       bool others = true;
       if (!bp_.empty()) NEP_TRY(reject_bordered(st, others));
       if (others) NEP_TRY(run_fallback<double>(st));
     }
   }
+  NEP_TRY(join());
   NEP_HIP(launch_moments(pd, pre, pt_.moments, na_, Y, st));
   return NEP_OK;
 }
