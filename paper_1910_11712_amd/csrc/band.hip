@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64, 1) void k_band_lu(const ProbDesc* __restrict__ 
     process(b1, r0 + U);
   }
   info[g] = zp;
-  pmin[g] = sqrt(m2);
+  if (pmin != nullptr) pmin[g] = sqrt(m2);
 }
 
 // ---------------------------------------------------------------------------

@@ -133,17 +133,6 @@ __device__ __forceinline__ floatx16 bd_zero() {
   return z;
 }
 
-__device__ __forceinline__ unsigned bd_wave_max(unsigned v) {
-  int x = (int)v;
-  auto mx = [](int a, int b) { return (int)max((unsigned)a, (unsigned)b); };
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false));
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false));
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));
-  return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
 __device__ __forceinline__ float bd_readlane(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
@@ -216,7 +205,7 @@ __global__ __launch_bounds__(kBdLuThreads) void k_bd_lu(const BdProb* __restrict
 #pragma unroll
       for (int x = 0; x < B; ++x) {
         const unsigned key = used ? 0u : __float_as_uint(fabsf(a[x].re) + fabsf(a[x].im)) + 1u;
-        const unsigned best = bd_wave_max(key);
+        const unsigned best = wave_max_u32(key);
         const int pl = __ffsll((unsigned long long)__ballot(key == best)) - 1;  // lowest row on ties
         const c64 piv = {bd_readlane(a[x].re, pl), bd_readlane(a[x].im, pl)};
         if (lane == x) {
@@ -859,8 +848,9 @@ __global__ __launch_bounds__(512) void k_bd_apply(const BdProb* __restrict__ bp,
 }
 
 // Smallest pivot modulus, log|det T| and arg det T per node from the chunks'
-// and the border's pivots: det of the bordered matrix is (-1)^rp det T (the
-// border's unit diagonal of padded columns included).
+// and the border's pivots: det of the bordered matrix is det T (times
+// (-1)^rp, rp a multiple of 32: the border's -1 diagonal, padded columns
+// included).
 __global__ __launch_bounds__(64) void k_bd_pivots(const BdProb* __restrict__ bp, const int* __restrict__ prefix,
                                                   int cnt, const ProbDesc* __restrict__ pd,
                                                   const c64* __restrict__ pivots,
@@ -918,7 +908,7 @@ __global__ __launch_bounds__(64) void k_bd_pivots(const BdProb* __restrict__ bp,
     pmin[g] = m;
     if (det != nullptr) {
       det[g] = la;
-      det[nnodes + g] = remainder(ar + ((q.rp & 1) ? M_PI : 0.0), 2.0 * M_PI);
+      det[nnodes + g] = remainder(ar, 2.0 * M_PI);
     }
   }
 }

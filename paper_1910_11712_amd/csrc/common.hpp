@@ -172,6 +172,34 @@ const char* last_error();
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 inline long long ceil_div_ll(long long a, long long b) { return (a + b - 1) / b; }
 
+// Maximum / minimum of a 32-bit value over the wave with DPP row operations
+// (quad swaps, half-row and row mirrors, then the row broadcasts that carry
+// rows 0-2 into row 3); lane 63 holds the result, returned uniform.  Lanes a
+// broadcast does not reach keep their value (the "old" operand is the
+// operation's identity).
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  int x = (int)v;
+  auto mx = [](int a, int b) { return (int)max((unsigned)a, (unsigned)b); };
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false));  // row_half_mirror
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false));  // row_mirror
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));  // row_bcast15 -> rows 1, 3
+  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));  // row_bcast31 -> rows 2, 3
+  return (unsigned)__builtin_amdgcn_readlane(x, 63);
+}
+__device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
+  int x = (int)v;
+  auto mn = [](int a, int b) { return (int)min((unsigned)a, (unsigned)b); };
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0xB1, 0xF, 0xF, false));
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x4E, 0xF, 0xF, false));
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x141, 0xF, 0xF, false));
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x140, 0xF, 0xF, false));
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xA, 0xF, false));
+  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xC, 0xF, false));
+  return (unsigned)__builtin_amdgcn_readlane(x, 63);
+}
+
 // Device binary search: largest k with prefix[k] <= x (prefix[0] = 0).
 __device__ __forceinline__ int find_slot(const int* prefix, int cnt, int x) {
   int lo = 0, hi = cnt;  // prefix[lo] <= x < prefix[hi]

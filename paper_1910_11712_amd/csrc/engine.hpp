@@ -149,7 +149,7 @@ int band_class(int w);    // window half-width (1, 2 or 4) that holds a band of 
 int band_entries(int W);  // stored entries per row and node
 void band_tables(BandTables& bt, std::vector<int>& buf, const std::vector<ProbDesc>& pd);
 // assembly and factorization of every band problem's nodes (skip: nodes left
-// out); info: first zero pivot or n, pmin: smallest pivot modulus, per node
+// out); info: first zero pivot or n, pmin (may be null): smallest pivot modulus, per node
 template <typename P>
 hipError_t band_factor(const BandTables& bt, const ProbDesc* pd, const int* prefix, const NodeArrays& na, cx<P>* F,
                        unsigned char* piv, int* info, double* pmin, const int* skip, hipStream_t st);

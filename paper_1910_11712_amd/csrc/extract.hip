@@ -729,7 +729,7 @@ static EtaBuffers eta_carve(char* small, c128* Rt, int m) { return EtaBuffers{sm
 // the split-form residuals T(lambda_q) x_q and the column maxima into b; the
 // host reads them back and forms
 // eta_q = max|T x| / (sum_i |f_i| ||A_i||_inf max|x|).
-// host: eta_small_bytes of host memory.
+// host: room for the larger of b's two blocks.
 static nep_status eta_run(Split& h, int m, const c128* lam, const c128* X, const EtaBuffers& b, char* host, double* eta,
                           hipStream_t st) {
   const int n = h.op.n, ell = h.op.ell;
@@ -856,11 +856,15 @@ static nep_status backward_errors_noalloc(Split& h, int m, const double* lambda,
                         sizeof(int) * kNoAllocMaxPairs + sizeof(double) * 2 * kNoAllocMaxPairs + 2 * 256 <=
                     kNoAllocSmall,
                 "small scratch region too small");
+  // the two host blocks take turns
+  constexpr size_t kNoAllocHost = sizeof(c128) * kNoAllocMaxPairs * kMaxTerms + sizeof(double) * 2 * kNoAllocMaxPairs +
+                                  sizeof(int) * kNoAllocMaxPairs;
+  static_assert(kEtaTerms + sizeof(c128) * kNoAllocMaxPairs <= kNoAllocHost, "host block too small");
   void* base = nullptr;
   NEP_TRY(scratch_address(&base));
   char* p = static_cast<char*>(base);
   const EtaBuffers b = eta_carve(p + kNoAllocMaxResid * sizeof(c128), reinterpret_cast<c128*>(p), m);
-  alignas(16) char host[kNoAllocSmall];  // on the stack (bounded by the limits above)
+  alignas(16) char host[kNoAllocHost];  // on the stack (bounded by the limits above)
   return eta_run(h, m, reinterpret_cast<const c128*>(lambda), X, b, host, eta, h.stream);
 }
 

@@ -227,34 +227,6 @@ __device__ __forceinline__ unsigned pivot_key(double v) {
   return (unsigned)((unsigned long long)__double_as_longlong(v) >> 32) + 1u;
 }
 
-// Maximum / minimum of a 32-bit value over the wave with DPP row operations
-// (quad swaps, half-row and row mirrors, then the row broadcasts that carry
-// rows 0-2 into row 3); lane 63 holds the result, returned uniform.  Lanes a
-// broadcast does not reach keep their value (the "old" operand is the
-// operation's identity).
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
-  int x = (int)v;
-  auto mx = [](int a, int b) { return (int)max((unsigned)a, (unsigned)b); };
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false));  // row_half_mirror
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false));  // row_mirror
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));  // row_bcast15 -> rows 1, 3
-  x = mx(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));  // row_bcast31 -> rows 2, 3
-  return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
-__device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
-  int x = (int)v;
-  auto mn = [](int a, int b) { return (int)min((unsigned)a, (unsigned)b); };
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0xB1, 0xF, 0xF, false));
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x4E, 0xF, 0xF, false));
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x141, 0xF, 0xF, false));
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x140, 0xF, 0xF, false));
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xA, 0xF, false));
-  x = mn(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xC, 0xF, false));
-  return (unsigned)__builtin_amdgcn_readlane(x, 63);
-}
-
 // Leaf rows between the row-major factor and the LDS block S (one chunk of
 // NT logical rows from rbase, NT the panel group's threads).  A row's W-column segment is 128
 // bytes (64 for the 8-rows-per-thread leaves) split into 16-byte pieces, one

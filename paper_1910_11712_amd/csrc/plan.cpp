@@ -576,7 +576,6 @@ nep_status MomentsPlan::rebind_members(const std::vector<int>& member, const std
 void MomentsPlan::release_fallback() {
   dF64_.release();
   dpiv64_.release();
-  dpmin64_.release();
   dT64_.release();
   ddinv64_.release();
   dlinv64_.release();
@@ -1001,14 +1000,12 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
       if (s == NEP_OK) s = dlinv64_.alloc(2 * sizeof(c128) * (size_t)sorted_.size() * kLuMaxJB * kLuMaxJB);
       if (s == NEP_OK) s = dF64_.alloc(sizeof(c128) * (size_t)f_elems_);
       if (s == NEP_OK) s = dpiv64_.alloc(dpiv_.bytes);
-      if (s == NEP_OK) s = dpmin64_.alloc(dpmin_.bytes);
       if (s != NEP_OK) {
         dT64_.release();
         ddinv64_.release();
         dlinv64_.release();
         dF64_.release();
         dpiv64_.release();
-        dpmin64_.release();
       }
       return s;
     };
@@ -1071,8 +1068,7 @@ nep_status MomentsPlan::run_fallback(hipStream_t st) {
   // band problems: their unconverged nodes in FP64, over the band again
   unsigned char* piv = dpiv64_.as<unsigned char>();
   if (any_band_)
-    NEP_HIP(band_factor<double>(bt_, pd, pre, na_, dF64_.as<c128>(), piv, dinfo_.as<int>(), dpmin64_.as<double>(),
-                                skip, st));
+    NEP_HIP(band_factor<double>(bt_, pd, pre, na_, dF64_.as<c128>(), piv, dinfo_.as<int>(), nullptr, skip, st));
   NEP_HIP(solve_run<double>(sp_, pd, md, na_, T, drows_.as<int>(), Dinv, doff, nullptr, dY_.as<c128>(), false,
                             skip, ir_, st));
   if (any_band_)

@@ -264,7 +264,7 @@ class MomentsPlan {
   BandTables bt_;                     // band problems (band.hip)
   bool any_band_ = false;
   DevMem dbw_;                        // FP32 factors: the forward sweep's results
-  DevMem dF_, dF64_, dpiv_, dpiv64_, dpmin_, dpmin64_;   // their factors, pivots and smallest pivot moduli
+  DevMem dF_, dF64_, dpiv_, dpiv64_, dpmin_;   // their factors, pivots and smallest pivot moduli
   long long f_elems_ = 0;
   // bordered problems (border.hip): their factors, and their border systems'
   // LU and solve (node g of the plan is node g there)
