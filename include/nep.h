@@ -169,7 +169,9 @@ typedef struct {
 typedef struct {
   int N;                  /* nodes processed                                     */
   int refine_sweeps;      /* sweeps run (max over nodes)                         */
-  int n_fallback;         /* nodes re-solved in FP64                             */
+  int n_fallback;         /* nodes re-solved: in FP64, or with dense factors where
+                             those over band and border were rejected (calls that
+                             follow on the same nodes start from the dense ones)  */
   int n_unconverged;      /* nodes not meeting refine_tol after all sweeps       */
   int singular_node;      /* first node with an exact zero pivot, or -1          */
   int bad_node;           /* first node on a pole/branch cut, or -1              */
@@ -181,7 +183,8 @@ typedef struct {
   double min_abs_pivot;   /* smallest |u_kk| over the node factorizations in the
                              path's precision (complex FP32 for the mixed path),
                              of the band or of the chunks and the border where
-                             the terms are factored that way;
+                             the terms are factored that way (of the dense factors
+                             where those were rejected);
                              0 with NEP_ERR_SINGULAR, NaN if a factor holds NaN  */
 } nep_ciss_stats;
 
@@ -452,7 +455,8 @@ nep_status nep_nleigs_interp(nep_split h, const nep_contour* g, const nep_nleigs
  * the k x k Hessenberg matrix inside g whose Ritz vectors x (the first block,
  * 2-norm 1, largest entry real positive) have backward error (eq.
  * (sressplit), infinity norms) <= eta_tol are returned, sorted by real then
- * imaginary part.
+ * imaginary part, where real parts of neighbours that differ by at most 1e-10
+ * of the modulus (a conjugate pair's, by rounding) count as equal.
  *   W0: device, complex n x dmax column-major: the first d columns are the d
  *       parts w^0..w^{d-1} of the starting vector (they must be linearly
  *       independent).
@@ -504,12 +508,12 @@ nep_status nep_batch_create(int nprob, const nep_split* h,
  * non-NULL the call is synchronous (it ends with nep_batch_wait).  If NULL it
  * returns after enqueueing; nep_batch_wait must then follow before the
  * moments are used: the run does a fixed number of refinement sweeps on the
- * device, and nodes still above the tolerance are re-solved in FP64 there. */
+ * device, and nodes still above the tolerance are re-solved there. */
 nep_status nep_batch_run(nep_batch b, nep_ciss_stats* st);
 
-/* Waits for the last nep_batch_run, re-solves in FP64 the nodes its sweeps
- * left above the refinement tolerance (mixed precision with fp64_fallback),
- * and reports per-problem stats in st (optional, nprob entries) and the
+/* Waits for the last nep_batch_run, re-solves the nodes its sweeps left above
+ * the refinement tolerance (mixed precision with fp64_fallback; in FP64, or
+ * with dense factors in place of rejected band-and-border ones), and reports per-problem stats in st (optional, nprob entries) and the
  * status: the most severe of NEP_ERR_NOT_HOLOMORPHIC, NEP_ERR_SINGULAR,
  * NEP_ERR_REFINE over the problems.  NEP_ERR_ARG if no run is pending. */
 nep_status nep_batch_wait(nep_batch b, nep_ciss_stats* st);

@@ -169,7 +169,13 @@ hipError_t band_logdet(const BandTables& bt, const ProbDesc* pd, const int* pref
 // The bordered path (border.hip): one descriptor per problem that takes it.
 constexpr int kBdBlk = 32;                            // block rows, and the widest band
 constexpr int kBdMaxBlocks = (4096 + kBdBlk - 1) / kBdBlk;
-constexpr int kBdMinN = 256, kBdMinRatio = 4;         // matrix size, and its ratio to the border's, from which it is taken
+// Matrix size, and its ratio to the border's, from which the path is taken.  At
+// the line the dense path is behind everywhere it was measured (us a call,
+// dense / bordered; half-width 32): one operator of 256 rows, rank 64, 32 nodes
+// of 8 columns 1266 / 1240, 512 rows, rank 128 2384 / 2088, 768 rows, rank 192
+// 3623 / 3024; 32 of 256 rows, rank 64 18 670 / 3725, 32 of 512 rows, rank 128
+// 30 046 / 7957; without low-rank terms 256 rows 1010 / 517.
+constexpr int kBdMinN = 256, kBdMinRatio = 4;
 constexpr int kBdMaxRank = 256;                       // sum of the low-rank terms' ranks
 struct BdProb {
   int prob, w, nb, nch;          // problem, half-width, blocks, chunks

@@ -1218,6 +1218,8 @@ nep_status MomentsPlan::finish(hipStream_t st, RunResult& out, bool allow_fallba
     return NEP_OK;
   };
   if (!all_dense()) NEP_TRY(read_back());
+  else
+    for (int g = 0; g < G; ++g) info[g] = hpd_[na_prob_host_[g]].n;
   const bool refined = opt.max_refine > 0;
   const bool mixed = opt.prec == NEP_PREC_C32_IR64;
   std::vector<int> excluded;  // unconverged nodes of problems that fail anyway, or go dense

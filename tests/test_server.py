@@ -340,3 +340,33 @@ def test_server_prices_the_path_that_a_query_takes(nep):
         assert len(got) == len(want) > 0
         assert np.max(np.abs(got - want)) <= 1e-9
     op.close()
+
+
+def test_server_keeps_the_dense_factors_of_rejected_operators(nep):
+    """Operators whose bordered factors the refinement rejects: the batch's
+    answers, then further probes of one of them on the resident (dense)
+    factors while the other sits out."""
+    from test_gpu_border import _weak_chunk
+    N, L, K, me = 256, 4, 2, 16
+    con = Contour.circle(5.05, 0.03)
+    pa, pb, plug = _weak_chunk(0.0), _weak_chunk(0.0, n=520), wl.delay_problem(600, tau=1.0, seed=7)
+    a, b, op = (nep.SplitOperator.from_problem(p) for p in (pa, pb, plug))
+    V = {id(p): (wl.probes(p.n, L, 5), wl.probes(p.n, L, 6)) for p in (pa, pb)}
+    ref = {(id(p), k): _alone(nep, o, con, V[id(p)][k], N, L, K, "mixed", me) for p, o in ((pa, a), (pb, b)) for k in (0, 1)}
+    srv = nep.Server(hbm_budget=6 << 30, max_inflight=16, nstreams=1)
+    try:
+        t0 = srv.submit(op, Contour.circle(-1.0, 0.4), wl.probes(600, 8, 20), 32, 8, 4)  # the next two queue behind it
+        t = [srv.submit(o, con, V[id(p)][0], N, L, K, max_eigs=me) for p, o in ((pa, a), (pb, b))]
+        srv.wait(t0)
+        first = [srv.wait(x) for x in t]
+        again = [srv.wait(srv.submit(o, con, V[id(p)][1], N, L, K, max_eigs=me)) for p, o in ((pa, a), (pb, b))]
+    finally:
+        srv.close()
+    for k, res in enumerate((first, again)):
+        for p, r in zip((pa, pb), res):
+            want = ref[(id(p), k)]
+            assert r["status"] == 0 and r["reused"] == (k == 1), (k, r["status"], r["reused"])
+            got, lam = r["lam"][r["inside"]], want["lam"][want["inside"]]
+            assert len(got) == len(lam) > 0 and np.max(np.abs(got - lam)) <= 1e-9, (got, lam)
+    for o in (a, b, op):
+        o.close()
