@@ -892,12 +892,12 @@ nep_status MomentsPlan::enqueue_t(hipStream_t st, bool eager, bool refactor) {
   const long long* doff = ddinv_off_.as<long long>();
   hipStream_t beside = beside_;
   if (beside != nullptr && !bp_.empty()) {
-    // A captured pass keeps the bordered problems on st.  What was captured
-    // when hipStreamEndCapture ended in a host fault is the bordered chain on a
-    // forked stream with a further fork inside, the look-ahead of its border's
-    // LU; why the runtime fails there is not known.  So under capture streams
-    // are forked off st and joined to st alone, as the dense LU's own two and
-    // the band chain's are, which fork nothing themselves.
+    // A captured pass keeps the bordered problems on st: a host fault in
+    // hipStreamEndCapture was seen with their chain on a forked stream.  Why
+    // the runtime fails there is not known; what that branch has and the band
+    // chain and the dense LU's two streams do not have is a fork inside the
+    // fork, the look-ahead of its border's LU.  Under capture streams are
+    // forked off st and joined to st alone.
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     NEP_HIP(hipStreamIsCapturing(st, &cs));
     if (cs != hipStreamCaptureStatusNone) beside = nullptr;
